@@ -411,9 +411,10 @@ __device__ __forceinline__ void seg_esp(const double (&v)[SEG], double (&e)[SEG 
 // group's L lanes) and the moments H_m += Re(c1 (T / P) init z^m), P this
 // lane's segment product.  With W = c1 init T / P and c0 = i c1 / tau,
 // Re(c0 T) = Re(W (A - i tau B) i / tau) = B Re(W) + A tau Im(W) / sg.
+// c = {c1ire, c1iim, c1tre, c1tim} of the frequency, staged in LDS.
 template <int SEG, int L>
 __device__ __forceinline__ void freq_pass_poly(const double (&e)[SEG + 1], double (&H)[SEG], const FreqPoly &fr,
-                                               double &we)
+                                               const double *c, double &we)
 {
     const double sg = fr.sg;
     constexpr int NE = SEG / 2;         // highest even degree 2 NE <= SEG
@@ -437,8 +438,8 @@ __device__ __forceinline__ void freq_pass_poly(const double (&e)[SEG + 1], doubl
         qi = fmaT(Tr, ii, Ti * ir);
     }
     // Re(W) and tau Im(W); Re(W z^(2n)) = sg^n Re(W), Re(W z^(2n+1)) = sg^n tau Im(W)
-    const double Cr = fmaT(fr.c1ire, qr, -fr.c1iim * qi);
-    const double Ci = fmaT(fr.c1tre, qi, fr.c1tim * qr);
+    const double Cr = fmaT(c[0], qr, -c[1] * qi);
+    const double Ci = fmaT(c[2], qi, c[3] * qr);
     we = fmaT(Cr, Bo, we);
     we = fmaT(Ci * fr.isg, A, we);
     double pw = 1.0;
@@ -539,6 +540,75 @@ __device__ __forceinline__ void seg_grad_from_moments(V (&v)[SEG], double (&H)[S
     }
 }
 
+// ---- frequencies chosen at the point (at-least-t in the FP64 polynomial form)
+//
+// The k + 1 roots of unity give the count's distribution exactly for every
+// point.  At a given point in the box far fewer do, to the same precision:
+// the number of true literals X has mean mu = sum p_i and variance S = sum
+// p_i q_i, p_i = (1 - l_i) / 2, and
+//  * by Bernstein's inequality P(X - mu >= d), P(mu - X >= d) <= exp(-d^2 /
+//    (2 (S + d / 3))) = e^-B at d = B/3 + sqrt(B^2/9 + 2 B S): all but e^-B
+//    of X lies in lo..hi = mu -+ d, of the others' count X - xi_i in lo - 1..hi,
+//    and N >= hi - lo + 2 points alias nothing into the window (N = k + 1
+//    nothing at all);
+//  * |q_i + p_i z|^2 = 1 - 4 p_i q_i sin^2(th/2) <= exp(-4 p_i q_i sin^2(th/2)):
+//    the transform at angle th is below exp(-2 S sin^2(th/2)), and the
+//    frequencies past 2 S sin^2(th/2) = B are left out.
+// e^-B is under the rounding of the sum of all k / 2 frequencies, so nothing
+// is lost, and any point of the box needs at most about 60 (64 .. 256
+// before): a narrow distribution needs few points, a wide one few
+// frequencies.  t < lo or t > hi + 1: the value is -1 or +1 and the gradient
+// 0 to the same bound.  Window and frequencies are those of all restarts of
+// the wave.  Points outside the box (and NaN) take lo = 0, hi = k; the
+// frequency bound holds for every real point.
+// With the window lo..lo + N - 1, u = exp(-2 pi i a / N) and the factor e^(i K
+// th/2) C^K of the K = L SEG positions taken out, the value coefficient 2 h_a =
+// 4 (u^lo - u^t) / (N (1 - u)) gives c1 = r D, r = -2 C^(K-1) init^-L / N and
+// D = z^(K+1-2 lo) - z^(K+1-2 t), z = exp(i pi a / N).
+// Measured: large instance (1982 constraints of 128..512 literals, 256 restarts,
+// uniform points) grouped FP64 launch 4.62 -> 1.74 ms; 1000 such
+// constraints at 150 points with four fifths of the variables at a face 1.52
+// -> 0.47 ms; error against 64 bits unchanged (FP64 evaluation 1.0e-15).
+struct NodeWindow {
+    int lo, hi;     // window of the count over the wave's restarts
+    float frac;     // share of the circle's frequencies needed (>= 1/2: all)
+};
+// s1, s: this lane's sums of p and p q; mx: its largest |l|
+template <int L>
+__device__ __forceinline__ NodeWindow node_window(float s1, float s, float mx, int k)
+{
+#pragma unroll
+    for (int d = 1; d < L; d <<= 1) {
+        s1 += __shfl_xor(s1, d, 64);
+        s += __shfl_xor(s, d, 64);
+        mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+    }
+    int lo = 0, hi = k;
+    float frac = 1.0f;
+    if (mx <= 1.0f && s > -1.0f) {   // false for NaN
+        const float sp = fmaxf(s, 0.0f) + 1e-2f;   // above the sums' rounding
+        const float d = NODE_B / 3 + sqrtf(NODE_B * NODE_B / 9 + 2 * NODE_B * sp) + 0.25f;
+        lo = max(0, (int)floorf(s1 - d));
+        hi = min(k, (int)ceilf(s1 + d));
+    }
+    const float sm = s - 0.3f;   // one literal left out, and the sums' rounding
+    if (2 * sm > NODE_B) frac = asinf(sqrtf(NODE_B / (2 * sm))) * 0.3183099f;
+#pragma unroll
+    for (int d = L; d < 64; d <<= 1) {
+        lo = min(lo, __shfl_xor(lo, d, 64));
+        hi = max(hi, __shfl_xor(hi, d, 64));
+        frac = fmaxf(frac, __shfl_xor(frac, d, 64));
+    }
+    NodeWindow w;
+    w.lo = __builtin_amdgcn_readfirstlane(lo);
+    w.hi = __builtin_amdgcn_readfirstlane(hi);
+    w.frac = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(frac)));
+    return w;
+}
+// Frequencies whose coefficients a wave stages in LDS at a time (one per lane).
+constexpr int STAGE_FREQS = 64;
+constexpr int STAGE_DOUBLES = 4 * STAGE_FREQS;
+
 // First frequency of wave w of fg that split a constraint's n1 form-1 and
 // nf - n1 form-2 frequencies (and the real chain, on the last wave) into
 // shares of about equal estimated VALU work.  Wave-uniform integer arithmetic.
@@ -592,7 +662,8 @@ __device__ __forceinline__ void waves_reduce(void *lds, int wg, int fg, int lane
 // values through LDS (`lds`: (fg - 1) * (SEG + 1) * 64 values) and wave 0
 // adds them in wave order and writes the results.  Read-only inputs are
 // separate __restrict__ arguments: the compiler may then read uniform
-// descriptors and coefficients through the scalar cache.  UC: the
+// descriptors and coefficients through the scalar cache.  stage: this wave's
+// STAGE_DOUBLES doubles of LDS (polynomial form only).  UC: the
 // root-of-unity bins take the unit-circle form (every frequency FORM 3).
 template <typename IO, typename CT, int SEG, int L, bool CPLX, bool UC = false>
 __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, const int unit,
@@ -600,7 +671,7 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                                           const int32_t *__restrict__ lits, const float *__restrict__ wts,
                                           const TypeT<CT> *__restrict__ types,
                                           const FreqT<CT> *__restrict__ freqs, const int fg_in, const int wg_in,
-                                          void *lds)
+                                          void *lds, double *stage = nullptr)
 {
     const int fg = CPLX ? fg_in : 1;
     const int wg = CPLX ? wg_in : 0;
@@ -684,6 +755,55 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
         if constexpr (POLY) {
             // FP64 root-of-unity products in the polynomial form: moments of
             // every frequency, then the positions' gradients from them
+            const bool nodes = ty.thr > 0;   // frequencies chosen at the point
+            const FreqPoly *fp = reinterpret_cast<const FreqPoly *>(freqs) + ty.tab;
+            const double2 *roots = nullptr;
+            int f0, f1, np = 1, rlo = 0, rthr = 0;
+            CT cst = ty.cst;
+            if (nodes) {
+                double s1 = 0, s2 = 0;
+                float mx = 0.f;
+#pragma unroll
+                for (int t = 0; t < SEG; ++t) {
+                    s1 += lv[t];
+                    s2 = fmaT(lv[t], lv[t], s2);
+                    mx = fmaxf(mx, fabsf((float)lv[t]));
+                }
+                const NodeWindow w = node_window<L>((float)(0.5 * (SEG - s1)), (float)(0.25 * (SEG - s2)), mx, k);
+                if (ty.thr < w.lo || ty.thr > w.hi + 1) {
+                    // certain for every restart of the wave; the waves that
+                    // share the unit's frequencies all leave it here
+                    if (wg == 0) {
+                        const CT wc = (CT)wts[d.orig];
+                        const CT certain = ty.thr < w.lo ? CT(-1) : CT(1);
+                        if (j == 0) facc = fmaT(wc, certain, facc);
+                        if (a.con_val != nullptr && j == 0 && bok) a.con_val[(size_t)d.orig * a.B + b] = (IO)certain;
+                        if (a.want_grad && bok) {
+                            const IO zero = (IO)(wc * CT(0));
+#pragma unroll
+                            for (int t = 0; t < SEG; ++t)
+                                if (t < nv) a.slot[(size_t)(d.off + i0 + t) * a.B + b] = zero;
+                        }
+                    }
+                    continue;
+                }
+                const int ni = node_index(min(w.hi - w.lo + 2, k + 1));
+                np = node_count(ni);
+                // an even number of frequencies: the loop takes two at a time
+                const int nf = min((np - 1) >> 1, ((int)(w.frac * (float)np) + 3) & ~1);
+                f0 = (nf * wg) / fg;
+                f1 = (nf * (wg + 1)) / fg;
+                cst = (CT)(2 * (ty.thr - w.lo) - np) / (CT)np;
+                // exponents of z, made positive by a multiple of its order 2 np
+                // (2 lo, 2 t <= 2 k + 2 <= K + 1 + 128 np)
+                rlo = L * SEG + 1 - 2 * w.lo + 128 * np;
+                rthr = L * SEG + 1 - 2 * ty.thr + 128 * np;
+                roots = reinterpret_cast<const double2 *>(freqs + ty.root) + node_roots(ni);
+                fp += node_freqs(ni);
+            } else {
+                f0 = freq_bound(wg, fg, ty.n1, ty.n1 + ty.n2, ty.has_real);
+                f1 = freq_bound(wg + 1, fg, ty.n1, ty.n1 + ty.n2, ty.has_real);
+            }
             double e[SEG + 1];
             seg_esp<SEG>(lv, e);
             double H[SEG];
@@ -692,21 +812,48 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                 H[t] = 0;
                 asm volatile("" : "+v"(H[t]));
             }
-            const int n1 = ty.n1, nf = ty.n1 + ty.n2;
-            const int f0 = freq_bound(wg, fg, n1, nf, ty.has_real);
-            const int f1 = freq_bound(wg + 1, fg, n1, nf, ty.has_real);
-            // two frequencies per iteration: their Horner chains, butterflies
-            // and divisions interleave (a loop with cross-lane moves is not
-            // unrolled by the compiler), one wait for both coefficient loads
-            const FreqPoly *fp = reinterpret_cast<const FreqPoly *>(freqs) + ty.tab;
-            int f = f0;
 #pragma unroll 1
-            for (; f + 1 < f1; f += 2) {
-                const FreqPoly fa = fp[f], fb = fp[f + 1];
-                freq_pass_poly<SEG, L>(e, H, fa, we);
-                freq_pass_poly<SEG, L>(e, H, fb, we);
+            for (int c0 = f0; c0 < f1; c0 += STAGE_FREQS) {
+                const int c1 = min(c0 + STAGE_FREQS, f1);
+                // the gradient coefficients of the next frequencies, one per
+                // lane: the loop reads them back at a uniform address
+                if (c0 + lane < c1) {
+                    const int f = c0 + lane;
+                    double4 c;
+                    if (nodes) {
+                        const NodeBase *nb = reinterpret_cast<const NodeBase *>(fp) + f;
+                        const double2 za = roots[(unsigned)((f + 1) * rlo) % (unsigned)(2 * np)];
+                        const double2 zb = roots[(unsigned)((f + 1) * rthr) % (unsigned)(2 * np)];
+                        const double dr = za.x - zb.x, di = za.y - zb.y;
+                        c = double4{nb->ri * dr, nb->ri * di, nb->rt * dr, nb->rt * di};
+                    } else {
+                        c = double4{fp[f].c1ire, fp[f].c1iim, fp[f].c1tre, fp[f].c1tim};
+                    }
+                    double *q = stage + 4 * lane;
+                    q[0] = c.x;
+                    q[1] = c.y;
+                    q[2] = c.z;
+                    q[3] = c.w;
+                }
+                // a wave's LDS operations complete in order: only the
+                // compiler has to keep theirs
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                // two frequencies per iteration: their Horner chains,
+                // butterflies and divisions interleave (a loop with cross-lane
+                // moves is not unrolled by the compiler), one wait for both
+                // coefficient loads
+                int f = c0;
+#pragma unroll 1
+                for (; f + 1 < c1; f += 2) {
+                    const FreqPoly fa = fp[f], fb = fp[f + 1];
+                    freq_pass_poly<SEG, L>(e, H, fa, stage + 4 * (f - c0), we);
+                    freq_pass_poly<SEG, L>(e, H, fb, stage + 4 * (f - c0) + 4, we);
+                }
+                if (f < c1) freq_pass_poly<SEG, L>(e, H, fp[f], stage + 4 * (f - c0), we);
+                __builtin_amdgcn_wave_barrier();
             }
-            if (f < f1) freq_pass_poly<SEG, L>(e, H, fp[f], we);
             if (ty.has_real && wg == fg - 1) {
                 // the chain prod l of the root z = -1 (alpha = 0, beta = 1;
                 // padding factors 1): its segment product is e_SEG and the
@@ -720,7 +867,7 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                 waves_reduce<CT, SEG>(lds, wg, fg, lane, H, we);
                 if (wg > 0) continue;
             }
-            we += ty.cst;
+            we += cst;
             const CT wc = (CT)wts[d.orig];
             if (j == 0) facc = fmaT(wc, we, facc);
             if (a.con_val != nullptr && j == 0 && bok) a.con_val[(size_t)d.orig * a.B + b] = (IO)we;
@@ -854,8 +1001,13 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<IO> a, const IO *__restri
     const bool split = CPLX && a.fg > 1;   // one unit per block, its frequencies over the waves
     const int unit = split ? (int)blockIdx.x : (int)blockIdx.x * (int)(blockDim.x >> 6) + wave;
     const Span sp{a.first, a.count, a.cpw, a.n_rb, a.fpart_row0};
+    double *stage = nullptr;
+    if constexpr (CPLX && sizeof(CT) == 8) {
+        __shared__ double stage_lds[4 * STAGE_DOUBLES];
+        stage = stage_lds + wave * STAGE_DOUBLES;
+    }
     eval_unit<IO, CT, SEG, L, CPLX>(a, sp, unit, xin, con, lits, wts, types, freqs, split ? a.fg : 1,
-                                    split ? wave : 0, eval_lds);
+                                    split ? wave : 0, eval_lds, stage);
 }
 
 template <typename IO>

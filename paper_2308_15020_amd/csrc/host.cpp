@@ -126,6 +126,8 @@ struct TypeD {
     int has_real = 0;
     int n1 = 0, n2 = 0;
     bool poly = false;   // FP64 root-of-unity type: its FP64 table takes the FreqPoly layout
+    int thr = 0;         // at-least-thr type whose frequencies are chosen at the point
+    int nf = 0;          // complex frequencies (chosen at the point: of a uniform random one)
     std::vector<FreqD> fr;
 };
 
@@ -228,6 +230,59 @@ TypeD dft_type(const std::vector<cld> &hv, int k, int L, int s, bool f64)
         }
     }
     return t;
+}
+
+// Frequencies that a uniform random point of a constraint of k literals
+// takes (the count's variance is k / 6 there), as node_window picks them.
+int node_freqs_uniform(int k)
+{
+    const double S = k / 6.0, B = NODE_B;
+    const double d = B / 3 + std::sqrt(B * B / 9 + 2 * B * S) + 0.25;
+    const int lo = std::max(0, (int)std::floor(0.5 * k - d)), hi = std::min(k, (int)std::ceil(0.5 * k + d));
+    const int np = node_count(node_index(std::min(hi - lo + 2, k + 1)));
+    const double frac = 2 * (S - 0.3) > B ? std::asin(std::sqrt(B / (2 * (S - 0.3)))) / (double)PI_L : 1.0;
+    return std::min((np - 1) / 2, ((int)(frac * np) + 3) & ~1);
+}
+
+// The NodeBase entries of every point count up to k + 1 for segments of s
+// positions on L lanes, and the roots of those counts.
+std::vector<FreqF64> node_base(int kmax, int L, int s)
+{
+    std::vector<FreqF64> out;
+    const int K = L * s;
+    for (int i = 0; i <= node_index(std::min(kmax, K) + 1); ++i) {
+        const int N = node_count(i);
+        for (int a = 1; a <= (N - 1) / 2; ++a) {
+            const long double half = PI_L * a / N;
+            const long double C = cosl(half), S = sinl(half);
+            const bool form1 = C >= S;
+            const long double tk = form1 ? S / C : C / S;
+            const int e = (int)floorl((long double)s * log2l(1.0L + tk * tk) / 4.0L);
+            // start value: 2^-e, and kappa^s where form 2 runs through form 1's code (dft_type)
+            const long double init = ldexpl(form1 ? 1.0L : powl(tk, (long double)s), -e);
+            const long double tau = S / C;
+            // -2 C^(K-1) init^-L / N
+            const long double r = -2.0L / N * ldexpl(powl(form1 ? C : S, (long double)K) / C, L * e);
+            const double taud = (double)tau, initd = (double)init, sg = -(taud * taud);
+            out.push_back(FreqF64{sg, 1.0 / sg, initd, initd * taud, (double)(r * init), (double)(r * init * tau), 0.0, 0.0});
+        }
+    }
+    return out;
+}
+std::vector<FreqF64> node_root_table(int kmax)
+{
+    std::vector<double> z;
+    for (int i = 0; i <= node_index(kmax + 1); ++i) {
+        const int N = node_count(i);
+        for (int j = 0; j < 2 * N; ++j) {
+            const long double ang = PI_L * j / N;
+            z.push_back((double)cosl(ang));
+            z.push_back((double)sinl(ang));
+        }
+    }
+    std::vector<FreqF64> out((z.size() + 7) / 8);
+    if (!z.empty()) memcpy((void *)out.data(), z.data(), z.size() * sizeof(double));
+    return out;
 }
 
 // ---- the unit-circle form (ablation of the basis above)
@@ -771,12 +826,19 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
         int ti;
         if (it == type_index.end()) {
             TypeD td;
-            if (cls == CLASS_DFT) {
+            if (cls == CLASS_DFT && ct == CT_F64 && !uc && kind != FFSAT_KIND_XOR && k >= NODE_MIN_LEN) {
+                // at-least-t (OR: t = 1): frequencies chosen at the point
+                td.cls = CLASS_DFT;
+                td.thr = kind == FFSAT_KIND_OR ? 1 : prm;
+                td.nf = node_freqs_uniform(k);
+            }
+            else if (cls == CLASS_DFT) {
                 auto key = std::make_tuple(tk.kind, tk.param, k);
                 auto mh = memo.find(key);
                 if (mh == memo.end())
                     mh = memo.emplace(key, uc ? uc_coeffs(tk.kind, tk.param, k) : conj_coeffs(tk.kind, tk.param, k)).first;
                 td = uc ? uc_type(mh->second, k, L, seg) : dft_type(mh->second, k, L, seg, ct == CT_F64);
+                td.nf = td.n1 + td.n2;
             }
             else if (rk == RK_OR) td = real_or();
             else if (rk == RK_XOR) td = real_xor(rparam);
@@ -809,7 +871,7 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
         } else {
             bidx = bi->second;
         }
-        const double cost = cls == CLASS_DFT ? (double)k * (double)(types[ti].n1 + types[ti].n2 + 1) * 9.0
+        const double cost = cls == CLASS_DFT ? (double)k * (double)(types[ti].nf + 1) * 9.0
                                              : (double)k * 4.0;
         Bin &b = bins[(size_t)bidx];
         // Algorithmic work per restart.  Running products (FP32, and the
@@ -822,9 +884,9 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
         double alg = 0.0;
         {
             const TypeD &td = types[(size_t)ti];
-            const double nfc = (double)(td.n1 + td.n2);
+            const double nfc = (double)td.nf;
             if (cls == CLASS_DFT && ct == CT_F64 && !uc) {
-                alg = poly_flops(seg, L, td.n1 + td.n2);
+                alg = poly_flops(seg, L, td.nf);
                 b.flops += alg;
             } else {
                 b.flops += 14.0 * k * nfc + 4.0 * nfc + (td.has_real ? 8.0 * k : 0.0);
@@ -917,8 +979,8 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
     for (const TypeD &td : types) {
         const int tab = (int)f64.size();
         TypeF32 a{(float)td.cst, (float)td.alpha, (float)td.beta, (float)td.c0r, (float)td.c1r,
-                  (float)td.pad, td.n1, td.n2, td.has_real, tab};
-        TypeF64 b{td.cst, td.alpha, td.beta, td.c0r, td.c1r, td.pad, td.n1, td.n2, td.has_real, tab};
+                  (float)td.pad, td.n1, td.n2, td.has_real, tab, 0, 0};
+        TypeF64 b{td.cst, td.alpha, td.beta, td.c0r, td.c1r, td.pad, td.n1, td.n2, td.has_real, tab, td.thr, 0};
         t32.push_back(a);
         t64.push_back(b);
         for (const FreqD &f : td.fr) {
@@ -937,6 +999,29 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
     // one entry of padding: the kernels prefetch the entry after a type's last
     f32.push_back(FreqF32{});
     f64.push_back(FreqF64{});
+    // types whose frequencies are chosen at the point: one base table per
+    // segment shape (several shapes may have the same L * SEG) and the roots
+    std::map<std::pair<int, int>, int> base_tab;
+    int root_tab = -1;
+    for (int q = 0; q < m; ++q) {
+        const Item &it = items[(size_t)q];
+        if (types[(size_t)it.type].thr == 0) continue;
+        const Bin &bn = bins[(size_t)it.bin];
+        if (root_tab < 0) {
+            root_tab = (int)f64.size();
+            const std::vector<FreqF64> z = node_root_table(p->maxk);
+            f64.insert(f64.end(), z.begin(), z.end());
+        }
+        const auto key = std::make_pair(bn.L, bn.seg);
+        auto bt = base_tab.find(key);
+        if (bt == base_tab.end()) {
+            bt = base_tab.emplace(key, (int)f64.size()).first;
+            const std::vector<FreqF64> nb = node_base(p->maxk, bn.L, bn.seg);
+            f64.insert(f64.end(), nb.begin(), nb.end());
+        }
+        t64[(size_t)it.type].tab = bt->second;
+        t64[(size_t)it.type].root = root_tab;
+    }
     Ly.n_types = (int)types.size();
     Ly.n_freqs = (int64_t)f64.size();
     ffsat_status st;

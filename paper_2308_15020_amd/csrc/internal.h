@@ -27,6 +27,10 @@ template <typename T>
 struct TypeT {
     T cst, alpha, beta, c0r, c1r, pad;
     int32_t n1, n2, has_real, tab;
+    // at-least-t types of the FP64 polynomial form whose frequencies are chosen
+    // at the point (thr = t > 0): tab is the NodeBase table of L * SEG
+    // positions and root the table of roots, both in the FP64 frequency array
+    int32_t thr, root;
 };
 // One complex frequency.  Form 1 (first n1 entries of a type): factor
 // psi = 1 - i*tk*l.  Form 2 (next n2 entries): psi = tk - i*l.  Each lane
@@ -45,6 +49,39 @@ struct FreqPoly {
     double sg, isg, init, itau, c1ire, c1iim, c1tre, c1tim;
 };
 static_assert(sizeof(FreqPoly) == sizeof(FreqT<double>), "one table for both layouts");
+// Point counts N the kernel may take for such a type, all odd: 9, 17, .., 129
+// (index 0..15), 145, 161, .., 257 (16..23), 289, 321, .., 513 (24..31); one
+// step is at most a ninth of N from 65 on.  node_freqs: frequencies of the
+// counts before index i (a = 1..(N - 1)/2 each); the roots exp(i pi j / N),
+// j < 2 N, of the counts before it take 4 node_freqs + 2 i entries.
+constexpr int NODE_COUNTS = 32;
+__host__ __device__ constexpr int node_count(int i)
+{
+    return i < 16 ? 9 + 8 * i : (i < 24 ? 145 + 16 * (i - 16) : 289 + 32 * (i - 24));
+}
+__host__ __device__ constexpr int node_index(int w)   // smallest count >= w, w <= 513
+{
+    return w <= 9 ? 0 : (w <= 129 ? (w - 2) >> 3 : (w <= 257 ? 16 + ((w - 130) >> 4) : 24 + ((w - 258) >> 5)));
+}
+__host__ __device__ constexpr int node_freqs(int i)
+{
+    return i <= 16 ? 2 * i * (i + 1)
+                   : (i <= 24 ? 544 + (i - 16) * (4 * (i - 16) + 68) : 1344 + (i - 24) * (8 * (i - 24) + 136));
+}
+__host__ __device__ constexpr int node_roots(int i) { return 4 * node_freqs(i) + 2 * i; }
+// Frequency a of N points on segments of K = L * SEG positions: the first
+// four fields of FreqPoly, and c1 init / D, c1 init tau / D of the
+// coefficient c1 = r D, D the difference of two roots (eval_kernel.h).
+struct NodeBase {
+    double sg, isg, init, itau, ri, rt, unused0, unused1;
+};
+static_assert(sizeof(NodeBase) == sizeof(FreqPoly), "one array for both entries");
+// Truncation of the count's distribution and of its transform: exp(-NODE_B)
+// = 5.7e-19, below the rounding of a sum of terms of modulus up to 1.
+constexpr float NODE_B = 42.0f;
+// Shortest at-least-t constraint whose frequencies are chosen at the point:
+// below, the window of a point is hardly narrower than k + 1.
+constexpr int NODE_MIN_LEN = 80;
 using TypeF32 = TypeT<float>;
 using TypeF64 = TypeT<double>;
 using FreqF32 = FreqT<float>;

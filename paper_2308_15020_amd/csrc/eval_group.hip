@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 {
     extern __shared__ __align__(16) char group_lds[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    __shared__ double stage[4 * STAGE_DOUBLES];
+    __shared__ double stage[4 * wave_doubles<float>(32)];   // 40 KB: 3 blocks of 4 waves a CU, as the registers allow
     const int2 bw = blk[blockIdx.x];
     const GroupEntry e = ent[__builtin_amdgcn_readfirstlane(bw.x)];
     const Span sp{e.first, e.count, e.cpw, e.n_rb, e.fpart_row0};
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
 #define X(ID, S, LL)                                                                                          \
     case ID:                                                                                                  \
         eval_unit<float, double, S, LL, true>(a, sp, unit, xin, con, lits, wts, types, freqs, fg, wg, group_lds, \
-                                             stage + wave * STAGE_DOUBLES);                                   \
+                                             stage + wave * wave_doubles<float>(32));                                 \
         break;
         FFSAT_GROUP64_SHAPES(X)
 #undef X

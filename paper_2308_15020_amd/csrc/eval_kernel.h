@@ -608,6 +608,10 @@ __device__ __forceinline__ NodeWindow node_window(float s1, float s, float mx, i
 // Frequencies whose coefficients a wave stages in LDS at a time (one per lane).
 constexpr int STAGE_FREQS = 64;
 constexpr int STAGE_DOUBLES = 4 * STAGE_FREQS;
+// LDS of a wave in the polynomial form, in doubles: the staged coefficients
+// and, with FP32 points, its seg literals per lane.
+template <typename IO>
+__host__ __device__ constexpr int wave_doubles(int seg) { return STAGE_DOUBLES + (sizeof(IO) == 4 ? 32 * seg : 0); }
 
 // First frequency of wave w of fg that split a constraint's n1 form-1 and
 // nf - n1 form-2 frequencies (and the real chain, on the last wave) into
@@ -663,7 +667,7 @@ __device__ __forceinline__ void waves_reduce(void *lds, int wg, int fg, int lane
 // adds them in wave order and writes the results.  Read-only inputs are
 // separate __restrict__ arguments: the compiler may then read uniform
 // descriptors and coefficients through the scalar cache.  stage: this wave's
-// STAGE_DOUBLES doubles of LDS (polynomial form only).  UC: the
+// wave_doubles<IO>(SEG) doubles of LDS (polynomial form only).  UC: the
 // root-of-unity bins take the unit-circle form (every frequency FORM 3).
 template <typename IO, typename CT, int SEG, int L, bool CPLX, bool UC = false>
 __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, const int unit,
@@ -804,6 +808,13 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                 f0 = freq_bound(wg, fg, ty.n1, ty.n1 + ty.n2, ty.has_real);
                 f1 = freq_bound(wg + 1, fg, ty.n1, ty.n1 + ty.n2, ty.has_real);
             }
+            float *keep = reinterpret_cast<float *>(stage + STAGE_DOUBLES);
+            if constexpr (sizeof(IO) == 4) {
+                if (a.want_grad && wg == 0) {
+#pragma unroll
+                    for (int t = 0; t < SEG; ++t) keep[t * 64 + lane] = (float)lv[t];
+                }
+            }
             double e[SEG + 1];
             seg_esp<SEG>(lv, e);
             double H[SEG];
@@ -873,19 +884,28 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
             if (a.con_val != nullptr && j == 0 && bok) a.con_val[(size_t)d.orig * a.B + b] = (IO)we;
             if (a.want_grad && bok) {
                 asm volatile("" : "+v"(nv));
-                // the literals again, from memory (L2): keeping them across
-                // the frequency loop would cost SEG registers there.  The
-                // opaque index keeps the compiler from reusing the first loads.
-                int ib = i0;
-                asm volatile("" : "+v"(ib));
-                int lr[SEG];
-#pragma unroll
-                for (int t = 0; t < SEG; ++t) lr[t] = lits[d.off + min(ib + t, k - 1)];
+                // the literals again: keeping them across the frequency loop
+                // would cost SEG registers there.  FP32 points wait in LDS (the
+                // second gather took as long as the first: a wave reads 16 or
+                // 32 bytes of each line, and its lines do not stay in the
+                // caches); FP64 ones are read from memory again (their LDS
+                // would halve the waves per CU).  The opaque index keeps the
+                // compiler from reusing the first loads.
                 IO lio[SEG];
+                if constexpr (sizeof(IO) == 4) {
 #pragma unroll
-                for (int t = 0; t < SEG; ++t) {
-                    const IO xv = xin[(size_t)(lr[t] & 0x7fffffff) * a.B + bb];
-                    lio[t] = t < nv ? (lr[t] < 0 ? -xv : xv) : (IO)ty.pad;
+                    for (int t = 0; t < SEG; ++t) lio[t] = keep[t * 64 + lane];
+                } else {
+                    int ib = i0;
+                    asm volatile("" : "+v"(ib));
+                    int lr[SEG];
+#pragma unroll
+                    for (int t = 0; t < SEG; ++t) lr[t] = lits[d.off + min(ib + t, k - 1)];
+#pragma unroll
+                    for (int t = 0; t < SEG; ++t) {
+                        const IO xv = xin[(size_t)(lr[t] & 0x7fffffff) * a.B + bb];
+                        lio[t] = t < nv ? (lr[t] < 0 ? -xv : xv) : (IO)ty.pad;
+                    }
                 }
                 seg_grad_from_moments<SEG>(lio, H, [&](int t, double g) {
                     if (t < nv) {
@@ -1003,8 +1023,8 @@ __global__ __launch_bounds__(256) void k_eval(EvalArgs<IO> a, const IO *__restri
     const Span sp{a.first, a.count, a.cpw, a.n_rb, a.fpart_row0};
     double *stage = nullptr;
     if constexpr (CPLX && sizeof(CT) == 8) {
-        __shared__ double stage_lds[4 * STAGE_DOUBLES];
-        stage = stage_lds + wave * STAGE_DOUBLES;
+        __shared__ double stage_lds[4 * wave_doubles<IO>(SEG)];
+        stage = stage_lds + wave * wave_doubles<IO>(SEG);
     }
     eval_unit<IO, CT, SEG, L, CPLX>(a, sp, unit, xin, con, lits, wts, types, freqs, split ? a.fg : 1,
                                     split ? wave : 0, eval_lds, stage);

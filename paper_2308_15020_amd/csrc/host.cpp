@@ -1291,6 +1291,40 @@ static bool in_group64(const Bin &b)
     return !b.uc && b.ct == CT_F64 && b.cls == CLASS_DFT && group_variant64(b.seg, b.L) >= 0;
 }
 
+struct Blk {
+    int2 b;         // entry, first unit
+    double cost;
+    int con;        // (entry, chunk) key: blocks of one key read the same rows of x
+};
+// Orders blocks longest first so that the blocks of one key run on one XCD:
+// workgroup i is dispatched to XCD i mod 8, and neighbouring restart blocks
+// read parts of the same 128-byte lines of x, which otherwise enter several
+// XCDs' L2.  Keys go whole to the shortest of eight lists.
+static std::vector<int2> xcd_order(std::vector<Blk> &blk)
+{
+    constexpr size_t XCDS = 8;
+    std::stable_sort(blk.begin(), blk.end(), [](const Blk &x, const Blk &y) { return x.cost > y.cost; });
+    std::vector<int2> lists[XCDS];
+    for (size_t i = 0; i < blk.size();) {
+        size_t to = 0;
+        for (size_t q = 1; q < XCDS; ++q)
+            if (lists[q].size() < lists[to].size()) to = q;
+        const int key = blk[i].con;
+        for (; i < blk.size() && blk[i].con == key; ++i) lists[to].push_back(blk[i].b);
+    }
+    std::vector<int2> order;
+    order.reserve(blk.size());
+    size_t at[XCDS] = {};
+    while (order.size() < blk.size()) {
+        size_t q = order.size() % XCDS;
+        if (at[q] == lists[q].size())   // the list's tail is done: the longest rest
+            for (size_t r = 0; r < XCDS; ++r)
+                if (lists[r].size() - at[r] > lists[q].size() - at[q]) q = r;
+        order.push_back(lists[q][at[q]++]);
+    }
+    return order;
+}
+
 // Block table of the grouped FP32 evaluation (MODE_GROUP_ALL: every bin with
 // a grouped variant; MODE_GROUP_DFT: the root-of-unity bins, the others run
 // on a side stream beside it).  Units of a bin are (chunk,
@@ -1318,12 +1352,8 @@ static ffsat_status build_groups(ffsat_plan *pl)
     if (!pl->grouped) return FFSAT_OK;
     const std::vector<Bin> &bins = pl->bins[IO_F32];
     std::vector<GroupEntry> ent, ent64;
-    struct Blk {
-        int2 b;
-        double cost;
-    };
     std::vector<Blk> dft, real, f64;
-    int row0 = 0;
+    int row0 = 0, con0 = 0;   // con0: first key of the bin
     for (int i = 0; i < (int)bins.size(); ++i) {
         const Bin &b = bins[i];
         const int rows = (b.count + b.cpw - 1) / b.cpw;
@@ -1337,7 +1367,8 @@ static ffsat_status build_groups(ffsat_plan *pl)
             const int64_t units = (int64_t)rows * n_rb;
             const double unit_cost = b.cost / std::max(1, b.count) * b.cpw * rpw;
             for (int64_t u = 0; u < units; u += (b.fg == 4 ? 1 : 4))
-                f64.push_back({make_int2(ei, (int)u), b.fg == 4 ? unit_cost : 4 * unit_cost});
+                f64.push_back({make_int2(ei, (int)u), b.fg == 4 ? unit_cost : 4 * unit_cost, con0 + (int)(u / n_rb)});
+            con0 += rows;
             if (b.fg == 4) pl->glds64 = std::max(pl->glds64, (size_t)3 * (b.seg + 1) * 64 * sizeof(double));
             row0 += rows;
             continue;
@@ -1357,19 +1388,17 @@ static ffsat_status build_groups(ffsat_plan *pl)
         const int64_t units = (int64_t)rows * n_rb;
         const double unit_cost = b.cost / std::max(1, b.count) * b.cpw * rpw;
         if (fg == 4) {
-            for (int64_t u = 0; u < units; ++u) dft.push_back({make_int2(ei, (int)u), unit_cost});
+            for (int64_t u = 0; u < units; ++u) dft.push_back({make_int2(ei, (int)u), unit_cost, con0 + (int)(u / n_rb)});
             pl->glds = std::max(pl->glds, (size_t)3 * (b.seg + 1) * 64 * sizeof(float));
         } else {
             for (int64_t u = 0; u < units; u += 4)
-                (b.cls == CLASS_DFT ? dft : real).push_back({make_int2(ei, (int)u), 4 * unit_cost});
+                (b.cls == CLASS_DFT ? dft : real).push_back({make_int2(ei, (int)u), 4 * unit_cost, con0 + (int)(u / n_rb)});
         }
+        con0 += rows;
         row0 += rows;
     }
     if (!ent64.empty()) {
-        std::stable_sort(f64.begin(), f64.end(), [](const Blk &x, const Blk &y) { return x.cost > y.cost; });
-        std::vector<int2> order64;
-        order64.reserve(f64.size());
-        for (const Blk &q : f64) order64.push_back(q.b);
+        const std::vector<int2> order64 = xcd_order(f64);
         HIPCHK(hipMalloc(&pl->d_gent64, ent64.size() * sizeof(GroupEntry)));
         HIPCHK(hipMemcpy(pl->d_gent64, ent64.data(), ent64.size() * sizeof(GroupEntry), hipMemcpyHostToDevice));
         HIPCHK(hipMalloc(&pl->d_gblk64, order64.size() * sizeof(int2)));

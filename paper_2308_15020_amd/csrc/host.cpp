@@ -1438,25 +1438,31 @@ static hipError_t enqueue_bins(ffsat_plan *pl, int io, EvalArgs<IO> a, hipStream
     const std::vector<Bin> &bins = pl->bins[io];
     if constexpr (sizeof(IO) == 4) {
         if (pl->grouped && (pl->gblocks > 0 || pl->gblocks64 > 0)) {
-            // bins without a grouped variant: on a side stream beside the
-            // grouped launch when there is one, else before it
+            // the FP64 group on a side stream; the bins without a grouped
+            // variant beside it (they are bound by memory and the FP64 group is
+            // not: behind it, as before, they added their whole time), on a
+            // second side stream where the FP32 group has the caller's.  While
+            // profiling, everything runs on s: each launch's time is its own.
             hipError_t e;
-            hipStream_t ss = s;
-            // while profiling, everything runs on s: each launch's time is its own
-            const bool fork = pl->side[0] != nullptr && !pl->gsolo.empty() && !pl->profiling;
-            if (fork) {
+            bool solo = false;
+            for (int bi : pl->gsolo) solo = solo || bins[bi].pk < pk_limit;
+            const bool can = pl->side[0] != nullptr && !pl->profiling;
+            const bool fork64 = can && pl->gblocks64 > 0 && (solo || pl->gblocks > 0);
+            const bool fork_solo = can && solo && pl->gblocks > 0;
+            hipStream_t s64 = fork64 ? pl->side[0] : s, ss = fork_solo ? pl->side[1] : s;
+            if (fork64 || fork_solo) {
                 if ((e = hipEventRecord(pl->ev_fork, s)) != hipSuccess) return e;
-                if ((e = hipStreamWaitEvent(pl->side[0], pl->ev_fork, 0)) != hipSuccess) return e;
-                ss = pl->side[0];
+                if (fork64 && (e = hipStreamWaitEvent(s64, pl->ev_fork, 0)) != hipSuccess) return e;
+                if (fork_solo && (e = hipStreamWaitEvent(ss, pl->ev_fork, 0)) != hipSuccess) return e;
             }
             if (pl->gblocks64 > 0) {
                 // the long FP64 root-of-unity bins first: the heaviest work
                 a.types = (const void *)Ly.d_t64;
                 a.freqs = (const void *)Ly.d_f64;
                 ProfRec rec;
-                prof_begin(pl, ss, prof_active(pl, s), rec, io, -4);
-                e = launch_eval_group64_f32(a, pl->d_gent64, pl->d_gblk64, pl->gblocks64, pl->glds64, ss);
-                prof_end(pl, ss, rec);
+                prof_begin(pl, s64, prof_active(pl, s), rec, io, -4);
+                e = launch_eval_group64_f32(a, pl->d_gent64, pl->d_gblk64, pl->gblocks64, pl->glds64, s64);
+                prof_end(pl, s64, rec);
                 if (e != hipSuccess) return e;
             }
             for (int bi : pl->gsolo) {
@@ -1487,9 +1493,10 @@ static hipError_t enqueue_bins(ffsat_plan *pl, int io, EvalArgs<IO> a, hipStream
                 prof_end(pl, s, rec);
                 if (e != hipSuccess) return e;
             }
-            if (fork) {
-                if ((e = hipEventRecord(pl->ev_join[0], pl->side[0])) != hipSuccess) return e;
-                if ((e = hipStreamWaitEvent(s, pl->ev_join[0], 0)) != hipSuccess) return e;
+            for (int q = 0; q < 2; ++q) {
+                if (!(q == 0 ? fork64 : fork_solo)) continue;
+                if ((e = hipEventRecord(pl->ev_join[q], pl->side[q])) != hipSuccess) return e;
+                if ((e = hipStreamWaitEvent(s, pl->ev_join[q], 0)) != hipSuccess) return e;
             }
             return hipSuccess;
         }

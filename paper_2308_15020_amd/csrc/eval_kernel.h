@@ -546,16 +546,18 @@ __device__ __forceinline__ void seg_grad_from_moments(V (&v)[SEG], double (&H)[S
 // point.  At a given point in the box far fewer do, to the same precision:
 // the number of true literals X has mean mu = sum p_i and variance S = sum
 // p_i q_i, p_i = (1 - l_i) / 2, and
-//  * by Bernstein's inequality P(X - mu >= d), P(mu - X >= d) <= exp(-d^2 /
-//    (2 (S + d / 3))) = e^-B at d = B/3 + sqrt(B^2/9 + 2 B S): all but e^-B
-//    of X lies in lo..hi = mu -+ d, of the others' count X - xi_i in lo - 1..hi,
-//    and N >= hi - lo + 2 points alias nothing into the window (N = k + 1
-//    nothing at all);
+//  * by Bennett's inequality P(X - mu >= d), P(mu - X >= d) <= exp(-S h(d / S)),
+//    h(u) = (1 + u) ln(1 + u) - u, which is e^-B where h(d / S) = B / S.
+//    Newton's steps on the convex h come down to that d from above, from
+//    Bernstein's d = B/3 + sqrt(B^2/9 + 2 B S), so each is a bound.  All but
+//    e^-B of X lies in lo..hi = mu -+ d, of the others' count X - xi_i in lo -
+//    1..hi, and N >= hi - lo + 2 points alias nothing into the window (N = k
+//    + 1 nothing at all);
 //  * |q_i + p_i z|^2 = 1 - 4 p_i q_i sin^2(th/2) <= exp(-4 p_i q_i sin^2(th/2)):
 //    the transform at angle th is below exp(-2 S sin^2(th/2)), and the
 //    frequencies past 2 S sin^2(th/2) = B are left out.
 // e^-B is under the rounding of the sum of all k / 2 frequencies, so nothing
-// is lost, and any point of the box needs at most about 60 (64 .. 256
+// is lost, and any point of the box needs at most about 55 (64 .. 256
 // before): a narrow distribution needs few points, a wide one few
 // frequencies.  t < lo or t > hi + 1: the value is -1 or +1 and the gradient
 // 0 to the same bound.  Window and frequencies are those of all restarts of
@@ -587,7 +589,14 @@ __device__ __forceinline__ NodeWindow node_window(float s1, float s, float mx, i
     float frac = 1.0f;
     if (mx <= 1.0f && s > -1.0f) {   // false for NaN
         const float sp = fmaxf(s, 0.0f) + 1e-2f;   // above the sums' rounding
-        const float d = NODE_B / 3 + sqrtf(NODE_B * NODE_B / 9 + 2 * NODE_B * sp) + 0.25f;
+        const float inv = 1.0f / sp, y = NODE_B * inv;
+        float u = (NODE_B / 3 + sqrtf(NODE_B * NODE_B / 9 + 2 * NODE_B * sp)) * inv;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const float ln = __logf(1.0f + u);
+            u -= ((1.0f + u) * ln - u - y) / ln;
+        }
+        const float d = u * sp * 1.0001f + 0.25f;   // above the FP32 rounding
         lo = max(0, (int)floorf(s1 - d));
         hi = min(k, (int)ceilf(s1 + d));
     }

@@ -237,7 +237,9 @@ TypeD dft_type(const std::vector<cld> &hv, int k, int L, int s, bool f64)
 int node_freqs_uniform(int k)
 {
     const double S = k / 6.0, B = NODE_B;
-    const double d = B / 3 + std::sqrt(B * B / 9 + 2 * B * S) + 0.25;
+    double u = (B / 3 + std::sqrt(B * B / 9 + 2 * B * S)) / S;
+    for (int q = 0; q < 2; ++q) u -= ((1 + u) * std::log1p(u) - u - B / S) / std::log1p(u);
+    const double d = u * S + 0.25;
     const int lo = std::max(0, (int)std::floor(0.5 * k - d)), hi = std::min(k, (int)std::ceil(0.5 * k + d));
     const int np = node_count(node_index(std::min(hi - lo + 2, k + 1)));
     const double frac = 2 * (S - 0.3) > B ? std::asin(std::sqrt(B / (2 * (S - 0.3)))) / (double)PI_L : 1.0;

@@ -16,7 +16,12 @@ def window(l, k):
         s1, s = np.sum((1 - c) / 2), np.sum((1 - c * c) / 4)
         a, b = 0, k
         if np.max(np.abs(c)) <= 1 and s > -1:
-            d = B / 3 + np.sqrt(B * B / 9 + 2 * B * (max(s, 0) + 1e-2)) + 0.25
+            v = max(s, 0) + 1e-2
+            u = (B / 3 + np.sqrt(B * B / 9 + 2 * B * v)) / v
+            for _ in range(2):
+                u -= ((1 + u) * np.log1p(u) - u - B / v) / np.log1p(u)
+                assert (1 + u) * np.log1p(u) - u >= B / v * (1 - 1e-12)   # Newton stays above the root
+            d = u * v + 0.25
             a, b = max(0, int(np.floor(s1 - d))), min(k, int(np.ceil(s1 + d)))
         sm = s - 0.3
         lo, hi = min(lo, a), max(hi, b)
@@ -106,7 +111,7 @@ def test_points_of_the_box_need_few_frequencies():
     for dist in ("uniform", "settled", "corner", "one_sided", "zero"):
         for scale in (1.0, 0.7, 0.3):
             l = points(512, 1, dist, rng) * scale
-            assert evaluate(l, int(round(np.sum((1 - l) / 2))) or 1, 512)[2] <= 66
+            assert evaluate(l, int(round(np.sum((1 - l) / 2))) or 1, 512)[2] <= 60
 
 
 def test_point_counts_cover_every_length():

@@ -4,9 +4,9 @@
 //    fused with the projected step (App. A.3, Alg. 5: clip to [-1,1]);
 //  * two-level deterministic sum of objective partials (Def. 3), the second
 //    level over 16 waves per block of 64 restarts;
-//  * projected step; rounding of the variables (Alg. 1); adaptive weights
-//    (Prop. 3); weight gradient; small utilities.  The exact constraint
-//    check runs inside the evaluation kernels.
+//  * projected step; adaptive weights (Prop. 3); weight gradient; small
+//    utilities.  The exact check beside an evaluation runs inside the
+//    evaluation kernels, the check alone in check.hip.
 #include <algorithm>
 
 #include "internal.h"
@@ -197,24 +197,7 @@ hipError_t launch_step_f64(int64_t total, int B, double *x, const double *g,
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- rounding
-
-template <typename IO>
-__global__ void k_assign_bits(int n, int B, const IO *__restrict__ x, uint32_t *bits)
-{
-    const int wn = (n + 31) / 32;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)wn * B) return;
-    const int word = (int)(idx / B);
-    const int b = (int)(idx - (int64_t)word * B);
-    uint32_t w = 0;
-    for (int q = 0; q < 32; ++q) {
-        const int v = word * 32 + q;
-        if (v >= n) break;
-        if (x[(size_t)v * B + b] < IO(0)) w |= 1u << q;
-    }
-    bits[(size_t)b * wn + word] = w;
-}
+// ---------------------------------------------------------------- fills
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
 {
@@ -241,23 +224,6 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s)
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
     return hipGetLastError();
-}
-
-template <typename IO>
-static hipError_t assign_impl(int n, int B, const IO *x, uint32_t *bits, hipStream_t s)
-{
-    const int64_t tot = (int64_t)((n + 31) / 32) * B;
-    hipLaunchKernelGGL((k_assign_bits<IO>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, n, B, x, bits);
-    return hipGetLastError();
-}
-
-hipError_t launch_assign_bits_f32(int n, int B, const float *x, uint32_t *bits, hipStream_t s)
-{
-    return assign_impl<float>(n, B, x, bits, s);
-}
-hipError_t launch_assign_bits_f64(int n, int B, const double *x, uint32_t *bits, hipStream_t s)
-{
-    return assign_impl<double>(n, B, x, bits, s);
 }
 
 // ---------------------------------------------------------------- adaptive weights

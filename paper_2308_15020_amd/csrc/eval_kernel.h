@@ -761,7 +761,6 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                 if (lane == 0 && bal != 0ull) atomicAdd(&a.U[d.orig], (int)__popcll(bal));
             }
         }
-        if (!a.do_value) continue;
 
         CT gr[SEG];
         CT we = 0;
@@ -1009,7 +1008,7 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
     }
     if (j == 0 && bok && wg == 0) {
         const size_t row = (size_t)(sp.fpart_row0 + chunk) * a.B + b;
-        if (a.do_value) a.fpart[row] = (IO)facc;
+        a.fpart[row] = (IO)facc;
         if (a.want_check) a.cpart[row] = nunsat;
     }
 }

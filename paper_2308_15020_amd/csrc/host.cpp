@@ -1053,6 +1053,7 @@ static void free_problem(ffsat_problem *p)
     (void)hipFree(p->d_w);
     (void)hipFree(p->d_kind);
     (void)hipFree(p->d_param);
+    (void)hipFree(p->d_long);
     delete p;
 }
 
@@ -1090,6 +1091,14 @@ extern "C" ffsat_status ffsat_problem_create(const ffsat_problem_desc *d, ffsat_
         (st = upload(&p->d_param, params, p->device_bytes)) != FFSAT_OK ||
         (st = build_layout(p, d, IO_F32, memo)) != FFSAT_OK ||
         (st = build_layout(p, d, IO_F64, memo)) != FFSAT_OK) {
+        free_problem(p);
+        return st;
+    }
+    std::vector<int32_t> longer;
+    for (int q = 0; q < p->m; ++q)
+        if (p->lay[IO_F32].h_con[(size_t)q].k > CHECK_SHORT) longer.push_back(q);
+    p->n_long = (int32_t)longer.size();
+    if ((st = upload(&p->d_long, longer, p->device_bytes)) != FFSAT_OK) {
         free_problem(p);
         return st;
     }
@@ -1245,7 +1254,6 @@ static EvalArgs<IO> base_args(ffsat_plan *pl, int io, const IO *x, IO *con_val, 
     a.B = pl->B;
     a.wm = (p->m + 31) / 32;
     a.want_grad = want_grad ? 1 : 0;
-    a.do_value = 1;
     a.want_check = 0;
     a.fg = 1;
     return a;
@@ -1703,8 +1711,8 @@ static void clear_graphs(ffsat_plan *pl)
 
 template <typename IO>
 static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *con_val, int32_t *n_sat,
-                             uint32_t *unsat_bits, int32_t *U, bool do_value, float *x_step, float eta,
-                             hipStream_t s, const float *eta_dev = nullptr, const int32_t *skip = nullptr,
+                             uint32_t *unsat_bits, int32_t *U, float *x_step, float eta, hipStream_t s,
+                             const float *eta_dev = nullptr, const int32_t *skip = nullptr,
                              float *x_next = nullptr);
 
 // Switches the pull path to class c (PULL_OFF, PULL_LE7, PULL_LE3): builds
@@ -2013,6 +2021,9 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
         hipError_t e = hipMalloc(&pl->d_flag, sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&pl->d_umax, 1024 * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&pl->d_hyper, 2 * sizeof(float));
+        const size_t signs = sizeof(uint64_t) * (size_t)p->n * (size_t)sign_stride(B);
+        if (e == hipSuccess) e = hipMalloc(&pl->d_signs, signs);
+        pl->device_bytes += (int64_t)signs;
         if (e != hipSuccess) st = fail(FFSAT_E_NOMEM, "hipMalloc flag: %s", hipGetErrorString(e));
     }
     if (st == FFSAT_OK && !(opts && opts->reserved[0] == 1)) {
@@ -2123,6 +2134,7 @@ extern "C" ffsat_status ffsat_plan_destroy(ffsat_plan *pl)
     (void)hipFree(pl->d_umax);
     (void)hipFree(pl->d_cpart);
     (void)hipFree(pl->d_ctmp);
+    (void)hipFree(pl->d_signs);
     (void)hipFree(pl->d_scratch_x);
     (void)hipFree(pl->d_fz);
     (void)hipFree(pl->d_fg);
@@ -2216,9 +2228,9 @@ static ffsat_status check_finite(ffsat_plan *pl, const IO *x, hipStream_t s)
 
 // The pull path serves an FP32 evaluation that produces a gradient or a step
 // and no per-constraint values.
-static bool pull_on(const ffsat_plan *pl, int io, bool do_value, const void *con_val, bool grad_or_step)
+static bool pull_on(const ffsat_plan *pl, int io, const void *con_val, bool grad_or_step)
 {
-    return io == IO_F32 && pl->pull > 0 && do_value && con_val == nullptr && grad_or_step;
+    return io == IO_F32 && pl->pull > 0 && con_val == nullptr && grad_or_step;
 }
 
 // Objective / count rows an evaluation writes: the launched bins' rows (the
@@ -2298,32 +2310,68 @@ static ReduceArgs<IO> reduce_args(ffsat_plan *pl, int io, IO *grad, float *x_ste
     return r;
 }
 
+// The exact check alone (and the assignment bits): signs packed, then the
+// constraints on the packed signs.
+template <typename IO>
+static ffsat_status run_check(ffsat_plan *pl, const IO *x, uint32_t *assign_bits, int32_t *n_sat, uint32_t *unsat_bits,
+                              int32_t *U, hipStream_t s)
+{
+    const ffsat_problem *p = pl->p;
+    const Layout &Ly = p->lay[IO_F32];   // any layout holds the constraints; points of either type
+    const bool check = n_sat || unsat_bits || U;
+    if (!check && !assign_bits) return FFSAT_OK;
+    if constexpr (sizeof(IO) == 4) HIPCHK(launch_signs_f32(p->n, pl->B, x, pl->d_signs, assign_bits, s));
+    else HIPCHK(launch_signs_f64(p->n, pl->B, x, pl->d_signs, assign_bits, s));
+    if (!check) return FFSAT_OK;
+    CheckArgs a{};
+    a.con = Ly.d_con;
+    a.pos = Ly.d_pos;
+    a.lit = Ly.d_lit;
+    a.signs = pl->d_signs;
+    a.unsat_bits = unsat_bits;
+    a.U = U;
+    a.rows = n_sat ? pl->d_cpart : nullptr;
+    a.m = p->m;
+    a.B = pl->B;
+    a.stride = sign_stride(pl->B);
+    a.wm = (p->m + 31) / 32;
+    HIPCHK(launch_check(a, p->d_long, p->n_long, s));
+    if (!n_sat) return FFSAT_OK;
+    ReduceArgs<float> r{};
+    r.n = p->n;
+    r.B = pl->B;
+    r.m = p->m;
+    r.cpart = pl->d_cpart;
+    r.rows = check_rows(p->m, pl->B, p->n_long);
+    r.ctmp = pl->d_ctmp;
+    r.n_sat = n_sat;
+    HIPCHK(launch_reduce_f32(r, s));
+    return FFSAT_OK;
+}
+
 // One evaluation pass: optional value/gradient/objective outputs, optional
 // exact check of the same point, optional fused projected step (in place
 // into x_step; with the pull path, into x_next when given, else through
 // the plan's second point buffer and a copy back).
 template <typename IO>
 static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *con_val, int32_t *n_sat,
-                             uint32_t *unsat_bits, int32_t *U, bool do_value, float *x_step, float eta,
-                             hipStream_t s, const float *eta_dev, const int32_t *skip, float *x_next)
+                             uint32_t *unsat_bits, int32_t *U, float *x_step, float eta, hipStream_t s,
+                             const float *eta_dev, const int32_t *skip, float *x_next)
 {
     const int io = sizeof(IO) == 4 ? IO_F32 : IO_F64;
     const ffsat_problem *p = pl->p;
     const bool want_check = n_sat || unsat_bits || U;
-    if (!do_value && !want_check) return FFSAT_OK;
     if (U) HIPCHK(launch_fill_i32(U, p->m, 0, s));
     if (unsat_bits) HIPCHK(launch_fill_i32((int32_t *)unsat_bits, (int64_t)((p->m + 31) / 32) * pl->B, 0, s));
-    const bool grad_slots = do_value && (grad != nullptr || x_step != nullptr);
-    const int pull = pull_on(pl, io, do_value, con_val, grad_slots) ? pl->pull : 0;
-    EvalArgs<IO> a = base_args<IO>(pl, io, x, do_value ? con_val : nullptr, grad_slots);
-    a.do_value = do_value ? 1 : 0;
+    const bool grad_slots = grad != nullptr || x_step != nullptr;
+    const int pull = pull_on(pl, io, con_val, grad_slots) ? pl->pull : 0;
+    EvalArgs<IO> a = base_args<IO>(pl, io, x, con_val, grad_slots);
     a.want_check = want_check ? 1 : 0;
     a.unsat_bits = unsat_bits;
     a.U = U;
     a.skip = skip;
     HIPCHK(enqueue_bins<IO>(pl, io, a, s, pull ? pull : 3));
-    ReduceArgs<IO> r = reduce_args<IO>(pl, io, do_value ? grad : nullptr, do_value ? x_step : nullptr, eta, eta_dev,
-                                       skip, do_value ? F : nullptr, n_sat, pull);
+    ReduceArgs<IO> r = reduce_args<IO>(pl, io, grad, x_step, eta, eta_dev, skip, F, n_sat, pull);
     // profile records: -3 the pulled gradient, -1 the reduction (with the
     // pull path only the objective / count sums)
     ProfRec rec;
@@ -2358,7 +2406,7 @@ extern "C" ffsat_status ffsat_eval(ffsat_plan *pl, const float *x, float *F, flo
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
     if (!F && !grad && !con_val) return FFSAT_OK;
-    return run_eval<float>(pl, x, F, grad, con_val, nullptr, nullptr, nullptr, true, nullptr, 0.f, s);
+    return run_eval<float>(pl, x, F, grad, con_val, nullptr, nullptr, nullptr, nullptr, 0.f, s);
 }
 
 extern "C" ffsat_status ffsat_eval_check(ffsat_plan *pl, const float *x, float *F, float *grad, float *con_val,
@@ -2369,8 +2417,8 @@ extern "C" ffsat_status ffsat_eval_check(ffsat_plan *pl, const float *x, float *
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
-    const bool value = F || grad || con_val;
-    return run_eval<float>(pl, x, F, grad, con_val, n_sat, unsat_bits, U, value, nullptr, 0.f, s);
+    if (!F && !grad && !con_val) return run_check<float>(pl, x, nullptr, n_sat, unsat_bits, U, s);
+    return run_eval<float>(pl, x, F, grad, con_val, n_sat, unsat_bits, U, nullptr, 0.f, s);
 }
 
 extern "C" ffsat_status ffsat_eval_step(ffsat_plan *pl, float *x, float eta, float *F, int32_t *n_sat, int32_t *U,
@@ -2381,7 +2429,7 @@ extern "C" ffsat_status ffsat_eval_step(ffsat_plan *pl, float *x, float eta, flo
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
-    return run_eval<float>(pl, x, F, nullptr, nullptr, n_sat, nullptr, U, true, x, eta, s);
+    return run_eval<float>(pl, x, F, nullptr, nullptr, n_sat, nullptr, U, x, eta, s);
 }
 
 extern "C" ffsat_status ffsat_eval_f64(ffsat_plan *pl, const double *x, double *F, double *grad, double *con_val,
@@ -2393,7 +2441,7 @@ extern "C" ffsat_status ffsat_eval_f64(ffsat_plan *pl, const double *x, double *
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<double>(pl, x, s)) != FFSAT_OK) return st;
     if (!F && !grad && !con_val) return FFSAT_OK;
-    return run_eval<double>(pl, x, F, grad, con_val, nullptr, nullptr, nullptr, true, nullptr, 0.f, s);
+    return run_eval<double>(pl, x, F, grad, con_val, nullptr, nullptr, nullptr, nullptr, 0.f, s);
 }
 
 extern "C" ffsat_status ffsat_step(ffsat_plan *pl, float *x, const float *grad, const float *eta_B, float eta,
@@ -2503,8 +2551,7 @@ static hipError_t enqueue_steps(ffsat_plan *pl, float *x, int T, float *F_last, 
     const bool pp = pl->pull > 0;
     float *cur = x, *nxt = pl->d_xalt;
     for (int t = 0; t < T; ++t) {
-        if (run_eval<float>(pl, cur, t == T - 1 ? F_last : nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, true,
-                            cur, 0.f, s, pl->d_hyper, nullptr, pp ? nxt : nullptr) != FFSAT_OK)
+        if (run_eval<float>(pl, cur, t == T - 1 ? F_last : nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, cur, 0.f, s, pl->d_hyper, nullptr, pp ? nxt : nullptr) != FFSAT_OK)
             return hipErrorUnknown;
         if (pp) std::swap(cur, nxt);
     }
@@ -2572,7 +2619,7 @@ static hipError_t enqueue_iters(ffsat_plan *pl, float *x, int T, bool erwa, floa
     const bool pp = pl->pull > 0;
     float *cur = x, *nxt = pl->d_xalt;
     for (int t = 0; t < T; ++t) {
-        if (run_eval<float>(pl, cur, F, nullptr, nullptr, n_sat, nullptr, U, true, cur, 0.f, s, pl->d_hyper, nullptr,
+        if (run_eval<float>(pl, cur, F, nullptr, nullptr, n_sat, nullptr, U, cur, 0.f, s, pl->d_hyper, nullptr,
                             pp ? nxt : nullptr) != FFSAT_OK)
             return hipErrorUnknown;
         if (erwa) {
@@ -2608,7 +2655,6 @@ static hipError_t enqueue_iters_overlapped(ffsat_plan *pl, float *x, int T, bool
     if (U) ITER_CHK(launch_fill_i32(U, p->m, 0, s));
     for (int t = 0; t < T; ++t) {
         EvalArgs<float> a = base_args<float>(pl, IO_F32, cur, nullptr, true);
-        a.do_value = 1;
         a.want_check = want_check ? 1 : 0;
         a.unsat_bits = nullptr;
         a.U = U;
@@ -2685,11 +2731,7 @@ extern "C" ffsat_status ffsat_round_check(ffsat_plan *pl, const float *x, uint32
     hipStream_t s = (hipStream_t)stream;
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
-    if ((st = run_eval<float>(pl, x, nullptr, nullptr, nullptr, n_sat, unsat_bits, U, false, nullptr, 0.f, s)) !=
-        FFSAT_OK)
-        return st;
-    if (assign_bits) HIPCHK(launch_assign_bits_f32(pl->p->n, pl->B, x, assign_bits, s));
-    return FFSAT_OK;
+    return run_check<float>(pl, x, assign_bits, n_sat, unsat_bits, U, s);
 }
 
 extern "C" ffsat_status ffsat_round_check_f64(ffsat_plan *pl, const double *x, uint32_t *assign_bits,
@@ -2699,11 +2741,7 @@ extern "C" ffsat_status ffsat_round_check_f64(ffsat_plan *pl, const double *x, u
     hipStream_t s = (hipStream_t)stream;
     ffsat_status st = ensure_workspace(pl, IO_F64);
     if (st != FFSAT_OK) return st;
-    if ((st = run_eval<double>(pl, x, nullptr, nullptr, nullptr, n_sat, unsat_bits, U, false, nullptr, 0.f, s)) !=
-        FFSAT_OK)
-        return st;
-    if (assign_bits) HIPCHK(launch_assign_bits_f64(pl->p->n, pl->B, x, assign_bits, s));
-    return FFSAT_OK;
+    return run_check<double>(pl, x, assign_bits, n_sat, unsat_bits, U, s);
 }
 
 extern "C" ffsat_status ffsat_sat_weight(ffsat_plan *pl, const uint32_t *unsat_bits, const float *w, double *score,
@@ -2759,14 +2797,14 @@ static hipError_t enqueue_fista_iter(ffsat_plan *pl, float *x, float *y, float *
     hipError_t e;
     if ((e = launch_fill_i32(pending, max_ls + 1, 0, s)) != hipSuccess) return e;
     if ((e = launch_fista_begin(B, eta, active, searching, pending, s)) != hipSuccess) return e;
-    if (run_eval<float>(pl, y, pl->d_fFy, pl->d_fg, nullptr, nullptr, nullptr, nullptr, true, nullptr, 0.f, s, nullptr,
+    if (run_eval<float>(pl, y, pl->d_fFy, pl->d_fg, nullptr, nullptr, nullptr, nullptr, nullptr, 0.f, s, nullptr,
                         pending) != FFSAT_OK)
         return hipErrorUnknown;
     for (int q = 0; q < max_ls; ++q) {
         if ((e = launch_fista_trial(n, B, y, pl->d_fg, eta, searching, pl->d_fz, pl->d_fpartial, pending + q, s)) !=
             hipSuccess)
             return e;
-        if (run_eval<float>(pl, pl->d_fz, pl->d_fFz, nullptr, nullptr, nullptr, nullptr, nullptr, true, nullptr, 0.f, s,
+        if (run_eval<float>(pl, pl->d_fz, pl->d_fFz, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0.f, s,
                             nullptr, pending + q) != FFSAT_OK)
             return hipErrorUnknown;
         if ((e = launch_fista_accept(n, B, pl->d_fpartial, pl->d_fFy, pl->d_fFz, eta, searching, F,

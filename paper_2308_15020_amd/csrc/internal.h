@@ -188,6 +188,8 @@ struct ffsat_problem {
     float *d_w = nullptr;        // weights, original order
     int32_t *d_kind = nullptr;   // original order
     int32_t *d_param = nullptr;
+    int32_t *d_long = nullptr;   // binned (FP32 layout) positions of the constraints of more than CHECK_SHORT literals
+    int32_t n_long = 0;
     ffsat::Layout lay[2];
     int64_t device_bytes = 0;
     // host copy of the constraint set (original order)
@@ -213,7 +215,7 @@ struct EvalArgs {
     const void *types;
     const void *freqs;
     int B, first, count, cpw, n_rb, fpart_row0;
-    int want_grad, do_value, want_check, wm;
+    int want_grad, want_check, wm;
     int fg;                // root-of-unity bins: waves sharing one unit's frequencies (1, 2 or 4)
     const int32_t *skip;   // if set and *skip == 0, every wave returns at once (nothing to evaluate)
 };
@@ -270,6 +272,7 @@ struct ffsat_plan {
     void *d_ftmp[2] = {nullptr, nullptr};
     int32_t *d_cpart = nullptr;      // violated-count rows (shared by both precisions)
     int32_t *d_ctmp = nullptr;
+    uint64_t *d_signs = nullptr;     // [n][sign_stride(B)] packed signs of the exact check alone
     int fpart_rows[2] = {0, 0};
     int32_t *d_flag = nullptr;       // debug non-finite flag
     int32_t *d_umax = nullptr;       // [1024] partial maxima of the weight update
@@ -444,8 +447,28 @@ hipError_t launch_step_f32(int64_t total, int B, float *x, const float *g, const
                            float eta, hipStream_t s);
 hipError_t launch_step_f64(int64_t total, int B, double *x, const double *g,
                            const double *eta_b, double eta, hipStream_t s);
-hipError_t launch_assign_bits_f32(int n, int B, const float *x, uint32_t *bits, hipStream_t s);
-hipError_t launch_assign_bits_f64(int n, int B, const double *x, uint32_t *bits, hipStream_t s);
+// The exact check alone (check.hip): signs of x packed 64 restarts to a word
+// (row stride sign_stride(B) words; the assignment bits beside them if assign
+// is set), then the constraints on the packed signs.
+constexpr int CHECK_SHORT = 32;     // longest constraint one thread counts
+constexpr int CHECK_GROUPS = 4;     // most groups of 64 constraints per wave
+constexpr int CHECK_LONG_PER = 4;   // longer constraints per wave
+struct CheckArgs {
+    const ConDesc *con;        // binned order
+    const int32_t *pos;        // original -> binned
+    const int32_t *lit;
+    const uint64_t *signs;
+    uint32_t *unsat_bits;      // [B][wm] or null, every word written
+    int32_t *U;                // [m] or null, every entry written
+    int32_t *rows;             // violated-constraint rows [check_rows][B] or null
+    int m, B, stride, wm, gpw;
+};
+int sign_stride(int B);
+hipError_t launch_signs_f32(int n, int B, const float *x, uint64_t *signs, uint32_t *assign, hipStream_t s);
+hipError_t launch_signs_f64(int n, int B, const double *x, uint64_t *signs, uint32_t *assign, hipStream_t s);
+int check_rows(int m, int B, int n_long);
+// list: binned positions of the n_long constraints of more than CHECK_SHORT literals
+hipError_t launch_check(CheckArgs a, const int32_t *list, int n_long, hipStream_t s);
 hipError_t launch_erwa(int m, const int32_t *U, float *w, float alpha, const float *alpha_dev, int32_t *part,
                        hipStream_t s);
 hipError_t launch_set_f32x2(float *p, float a, float b, hipStream_t s);

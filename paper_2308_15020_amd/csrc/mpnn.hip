@@ -31,9 +31,8 @@ __device__ __forceinline__ short to_bf16(float f)
 // block lies inside [.., lim) and contiguous rows may be read as two
 // aligned 16-byte loads (vec), else element by element with stride st,
 // zero past lim.
-__device__ __forceinline__ s16x8_t load8_bf16(const float *p, size_t st, int k, int lim, bool ok, bool vec)
+__device__ __forceinline__ void load8(const float *p, size_t st, int k, int lim, bool ok, bool vec, float (&v)[8])
 {
-    float v[8];
     if (ok && vec && k + 8 <= lim) {
         const float4 x0 = *reinterpret_cast<const float4 *>(p);
         const float4 x1 = *reinterpret_cast<const float4 *>(p + 4);
@@ -43,6 +42,9 @@ __device__ __forceinline__ s16x8_t load8_bf16(const float *p, size_t st, int k, 
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q] = (ok && k + q < lim) ? p[(size_t)q * st] : 0.f;
     }
+}
+__device__ __forceinline__ s16x8_t round8(const float (&v)[8])
+{
     s16x8_t r;
 #pragma unroll
     for (int q = 0; q < 8; ++q) r[q] = to_bf16(v[q]);
@@ -61,11 +63,20 @@ __device__ __forceinline__ s16x8_t load8_bf16(const float *p, size_t st, int k, 
 // contiguous operand (opA rows for !TA, opB columns for TB) may be read as
 // 16-byte loads (base 16-byte aligned, leading dimension a multiple of 4;
 // slices and blocks start at multiples of 16).
+// Bound by the latency of the operand loads (a wave has one tile and few
+// neighbours).  TN products, whose loads are single elements, issue those of
+// four instructions together: at 8700 rows, H = 64 the weight product took 24 us
+// in 17 slices of one instruction at a time and takes 8 us in 64 slices of
+// four.  The forward product reads wide and is faster one at a time (9.9
+// against 11.5 us).
+// colsum (TN products, EPI 0): the blocks of the first row tile also add the
+// columns of opB over the slice in FP32 and write them as row M of C (a
+// layer's bias gradient beside its weight gradient; it took a pass of its own).
 template <bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(64) void k_gemm(int M, int N, int K, const float *__restrict__ A, int lda,
                                              const float *__restrict__ B, int ldb, float *C, int ldc,
                                              const float *__restrict__ bias, int kslice, size_t slice_stride,
-                                             int vec_a, int vec_b)
+                                             int vec_a, int vec_b, int colsum)
 {
     const int l = threadIdx.x;
     const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
@@ -78,17 +89,33 @@ __global__ __launch_bounds__(64) void k_gemm(int M, int N, int K, const float *_
     f32x16_t acc;
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-    for (int k0 = kb; k0 < ke; k0 += 16) {
-        const int k = k0 + kh;
-        const s16x8_t a = TA ? load8_bf16(A + (size_t)k * lda + ai, (size_t)lda, k, ke, aok, false)
-                             : load8_bf16(A + (size_t)ai * lda + k, 1, k, ke, aok, vec_a != 0);
-        const s16x8_t b = TB ? load8_bf16(B + (size_t)bj * ldb + k, 1, k, ke, bok, vec_b != 0)
-                             : load8_bf16(B + (size_t)k * ldb + bj, (size_t)ldb, k, ke, bok, false);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                      acc, 0, 0, 0);
+    constexpr int GEMM_STEPS = TA ? 4 : 1;
+    float cs = 0.f;
+    for (int k0 = kb; k0 < ke; k0 += 16 * GEMM_STEPS) {
+        float a[GEMM_STEPS][8], b[GEMM_STEPS][8];
+#pragma unroll
+        for (int u = 0; u < GEMM_STEPS; ++u) {
+            const int k = k0 + 16 * u + kh;
+            if (TA) load8(A + (size_t)k * lda + ai, (size_t)lda, k, ke, aok, false, a[u]);
+            else load8(A + (size_t)ai * lda + k, 1, k, ke, aok, vec_a != 0, a[u]);
+            if (TB) load8(B + (size_t)bj * ldb + k, 1, k, ke, bok, vec_b != 0, b[u]);
+            else load8(B + (size_t)k * ldb + bj, (size_t)ldb, k, ke, bok, false, b[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < GEMM_STEPS; ++u) {
+            if (TA && colsum) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) cs += b[u][q];
+            }
+            if (k0 + 16 * u < ke)   // uniform
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, round8(a[u])),
+                                                              __builtin_bit_cast(bf16x8_t, round8(b[u])), acc, 0, 0, 0);
+        }
     }
     const int j = j0 + (l & 31);
+    if (TA && colsum) cs += __shfl_xor(cs, 32, 64);
     if (j >= N) return;
+    if (TA && colsum && blockIdx.x == 0 && l < 32) C[blockIdx.z * slice_stride + (size_t)M * ldc + j] = cs;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int i = i0 + 8 * (q >> 2) + 4 * (l >> 5) + (q & 3);
@@ -118,7 +145,7 @@ int gemm_slices(int K, int splits)
 }
 
 hipError_t gemm(bool ta, bool tb, int epi, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                float *C, int ldc, const float *bias, int splits, size_t slice_stride, hipStream_t s)
+                float *C, int ldc, const float *bias, int splits, size_t slice_stride, hipStream_t s, bool colsum)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
     int kslice = gemm_kslice(K, splits);
@@ -129,7 +156,8 @@ hipError_t gemm(bool ta, bool tb, int epi, int M, int N, int K, const float *A, 
     const int vec_b = tb && ((uintptr_t)B % 16 == 0) && ldb % 4 == 0;
 #define LAUNCH(TA, TB, E)                                                                                   \
     hipLaunchKernelGGL((k_gemm<TA, TB, E>), grid, dim3(64), 0, s, M, N, K, A, lda, B, ldb, C, ldc, bias, kslice, \
-                       slice_stride, vec_a, vec_b)
+                       slice_stride, vec_a, vec_b, colsum ? 1 : 0)
+    if (colsum && (!ta || tb || epi != 0)) return hipErrorInvalidValue;
     if (epi == 0) {
         if (!ta && !tb) LAUNCH(false, false, 0);
         else if (!ta && tb) LAUNCH(false, true, 0);
@@ -143,42 +171,49 @@ hipError_t gemm(bool ta, bool tb, int epi, int M, int N, int K, const float *A, 
     return hipGetLastError();
 }
 
-// out[i] = sum_{s < S} part[s * stride + i]  (fixed order), optionally added to out
-__global__ void k_sum_slices(int64_t len, int S, const float *__restrict__ part, size_t stride, float *out, int add)
+// out[i] = sum_{s < S} part[s * stride + i] (fixed order); entries from len
+// on go to tail
+__global__ void k_sum_slices(int64_t len, int64_t len_tail, int S, const float *__restrict__ part, size_t stride,
+                             float *out, float *tail)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= len) return;
+    if (i >= len + len_tail) return;
     float acc = 0.f;
+#pragma unroll 16
     for (int s = 0; s < S; ++s) acc += part[(size_t)s * stride + i];
-    out[i] = add ? out[i] + acc : acc;
+    if (i < len) out[i] = acc;
+    else tail[i - len] = acc;
 }
 
-hipError_t sum_slices(int64_t len, int S, const float *part, size_t stride, float *out, bool add, hipStream_t s)
+hipError_t sum_slices(int64_t len, int S, const float *part, size_t stride, float *out, hipStream_t s, int64_t len_tail,
+                      float *tail)
 {
-    if (len <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, s, len, S, part, stride, out,
-                       add ? 1 : 0);
+    if (len + len_tail <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((len + len_tail + 63) / 64)), dim3(64), 0, s, len, len_tail, S, part,
+                       stride, out, tail);
     return hipGetLastError();
 }
 
 // Weighted incidence sums, one wave per destination row, lanes over the H
-// features.  Row r owns edges e = row_ptr[r] .. row_ptr[r+1]; the edge's slot
-// is edges[e] (or e itself when edges is null); its source row is
-// src_of[slot], its weight w[slot], its sign from the literal lit[slot].
-//  mode 0 (messages):  dst[r][dpos + f] = sum over positive edges of w * src[src][f]
-//                      dst[r][dneg + f] = sum over negative edges  (written)
-//                      and, with hcopy, dst[r][f] = hcopy[r][f] (the row's own state)
-//  mode 1 (transposes): dst[r][f] += sum_e w * src[src][(pos ? spos : sneg) + f]
+// features.  Row r owns edges e = row_ptr[r] .. row_ptr[r+1] with source row
+// src_of[e], weight w[e] and the sign of literal lit[e].
+//  MODE 0 (messages):  dst[r][H + f] = sum over positive edges of w * src[src][f]
+//                      dst[r][2H + f] = sum over negative edges
+//                      dst[r][f] = own[r * ostride + f] (the row's own state)
+//  MODE 1 (transposes): dst[r][f] = own[r * ostride + f] + sum_e w * src[src][(pos ?
+//                      1 : 2) H + f] where y[r][f] > 0, else 0 (own: the row's
+//                      own columns of the product's result, or null; y: the
+//                      layer's output, whose ReLU is taken back here)
 // The metadata of up to 64 edges is loaded lane-parallel (one edge per lane)
-// and broadcast with readlane, so that the feature loads of consecutive
+// and broadcast with readlane, so that the feature loads of eight consecutive
 // edges do not wait on each other's index loads; the terms are added in edge
 // order.
+template <int MODE>
 __global__ __launch_bounds__(256) void k_gather(int rows, int H, const int32_t *__restrict__ row_ptr,
-                                                const int32_t *__restrict__ edges, const int32_t *__restrict__ src_of,
-                                                const int32_t *__restrict__ lit, const float *__restrict__ w,
-                                                const float *__restrict__ src, int sstride, int spos, int sneg,
-                                                float *dst, int dstride, int dpos, int dneg, int mode,
-                                                const float *__restrict__ hcopy)
+                                                const int32_t *__restrict__ src_of, const int32_t *__restrict__ lit,
+                                                const float *__restrict__ w, const float *__restrict__ src, int sstride,
+                                                float *dst, int dstride, const float *__restrict__ own, int ostride,
+                                                const float *__restrict__ y)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = blockIdx.x * (blockDim.x >> 6) + wave;
@@ -189,119 +224,87 @@ __global__ __launch_bounds__(256) void k_gather(int rows, int H, const int32_t *
         const int f = f0 + lane;
         const bool fin = f < H;
         const int fc = fin ? f : 0;
+        const float ow = own != nullptr ? own[(size_t)r * ostride + fc] : 0.f;
+        const float yv = MODE == 1 ? y[(size_t)r * H + fc] : 0.f;
         float ap = 0.f, an = 0.f;
         for (int eb = e0; eb < e1; eb += 64) {
             const int e = eb + lane;
             int so = 0, pos = 1;
             float we = 0.f;
             if (e < e1) {
-                const int slot = edges ? edges[e] : e;
-                pos = lit[slot] >= 0 ? 1 : 0;
+                pos = lit[e] >= 0 ? 1 : 0;
                 // element offset of the feature row this edge reads
-                so = src_of[slot] * sstride + (mode == 0 ? spos : (pos ? spos : sneg));
-                we = w[slot];
+                so = src_of[e] * sstride + (MODE == 0 ? 0 : (pos ? H : 2 * H));
+                we = w[e];
             }
             const int cnt = min(64, e1 - eb);
-            int q = 0;
-            for (; q + 4 <= cnt; q += 4) {
-                float v[4], wq[4];
-                int pq[4];
+            constexpr int NQ = 8;
+            // past the last edge: a null edge (row 0, weight 0) is loaded and not added
+            for (int q = 0; q < cnt; q += NQ) {
+                float v[NQ], wq[NQ];
+                int pq[NQ];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
+                for (int t = 0; t < NQ; ++t) {
                     const int o = __builtin_amdgcn_readlane(so, q + t);
                     pq[t] = __builtin_amdgcn_readlane(pos, q + t);
                     wq[t] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, we), q + t));
                     v[t] = src[(size_t)o + fc];
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    if (mode == 0) {
-                        if (pq[t]) ap += wq[t] * v[t];
+                for (int t = 0; t < NQ; ++t) {
+                    if (q + t < cnt) {   // uniform
+                        if (MODE == 1 || pq[t]) ap += wq[t] * v[t];
                         else an += wq[t] * v[t];
-                    } else {
-                        ap += wq[t] * v[t];
                     }
-                }
-            }
-            for (; q < cnt; ++q) {
-                const int o = __builtin_amdgcn_readlane(so, q);
-                const int pq = __builtin_amdgcn_readlane(pos, q);
-                const float wq = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, we), q));
-                const float v = src[(size_t)o + fc];
-                if (mode == 0) {
-                    if (pq) ap += wq * v;
-                    else an += wq * v;
-                } else {
-                    ap += wq * v;
                 }
             }
         }
         if (!fin) continue;
-        if (mode == 0) {
-            dst[(size_t)r * dstride + dpos + f] = ap;
-            dst[(size_t)r * dstride + dneg + f] = an;
-            if (hcopy) dst[(size_t)r * dstride + f] = hcopy[(size_t)r * H + f];
+        float *o = dst + (size_t)r * dstride + f;
+        if (MODE == 0) {
+            o[0] = ow;
+            o[H] = ap;
+            o[2 * H] = an;
         } else {
-            dst[(size_t)r * dstride + f] += ap;
+            const float g = ow + ap;
+            o[0] = yv > 0.f ? g : 0.f;
         }
     }
 }
 
-hipError_t gather(int rows, int H, const int32_t *row_ptr, const int32_t *edges, const int32_t *src_of,
-                  const int32_t *lit, const float *w, const float *src, int sstride, int spos, int sneg, float *dst,
-                  int dstride, int dpos, int dneg, int mode, hipStream_t s, const float *hcopy)
+hipError_t gather(int mode, int rows, int H, const int32_t *row_ptr, const int32_t *src_of, const int32_t *lit,
+                  const float *w, const float *src, int sstride, float *dst, int dstride, const float *own, int ostride,
+                  const float *y, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, rows, H, row_ptr, edges, src_of,
-                       lit, w, src, sstride, spos, sneg, dst, dstride, dpos, dneg, mode, hcopy);
+    const dim3 grid((unsigned)((rows + 3) / 4));
+    if (mode == 0)
+        hipLaunchKernelGGL(k_gather<0>, grid, dim3(256), 0, s, rows, H, row_ptr, src_of, lit, w, src, sstride, dst, dstride,
+                           own, ostride, y);
+    else
+        hipLaunchKernelGGL(k_gather<1>, grid, dim3(256), 0, s, rows, H, row_ptr, src_of, lit, w, src, sstride, dst, dstride,
+                           own, ostride, y);
     return hipGetLastError();
 }
 
-// dZ = dH * (Y > 0), in place on dH; also copies the first H columns of a
-// dX buffer into dH when dx is given (dH = dx[:, :H] * (Y > 0)).
-__global__ void k_relu_back(int64_t total, int H, float *dH, const float *__restrict__ Y,
-                            const float *__restrict__ dx, int dxstride)
+// dZ = dX[:, :H] * (Y > 0): the own columns of a product's result taken back
+// through a ReLU
+__global__ void k_relu_back(int64_t total, int H, float *dZ, const float *__restrict__ Y, const float *__restrict__ dx,
+                            int dxstride)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
-    float g = dH[i];
-    if (dx) {
-        const int64_t r = i / H;
-        g = dx[(size_t)r * dxstride + (i - r * H)];
-    }
-    dH[i] = Y[i] > 0.f ? g : 0.f;
+    const int64_t r = i / H;
+    const float g = dx[(size_t)r * dxstride + (i - r * H)];
+    dZ[i] = Y[i] > 0.f ? g : 0.f;
 }
 
-hipError_t relu_back(int rows, int H, float *dH, const float *Y, const float *dx, int dxstride, hipStream_t s)
+hipError_t relu_back(int rows, int H, float *dZ, const float *Y, const float *dx, int dxstride, hipStream_t s)
 {
     const int64_t total = (int64_t)rows * H;
     if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_relu_back, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, total, H, dH, Y, dx,
-                       dxstride);
+    hipLaunchKernelGGL(k_relu_back, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, total, H, dZ, Y, dx, dxstride);
     return hipGetLastError();
-}
-
-// column sums of a rows x H matrix over fixed row slices: part[slice][f]
-__global__ void k_colsum_part(int rows, int H, const float *__restrict__ X, int rows_per_slice, float *part)
-{
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= H) return;
-    const int r0 = blockIdx.y * rows_per_slice, r1 = min(rows, r0 + rows_per_slice);
-    float acc = 0.f;
-    for (int r = r0; r < r1; ++r) acc += X[(size_t)r * H + f];
-    part[(size_t)blockIdx.y * H + f] = acc;
-}
-
-hipError_t colsum(int rows, int H, const float *X, float *part, int max_slices, float *out, hipStream_t s)
-{
-    int slices = std::max(1, std::min(max_slices, (rows + 255) / 256));
-    const int rps = (rows + slices - 1) / slices;
-    slices = std::max(1, (rows + rps - 1) / rps);
-    hipLaunchKernelGGL(k_colsum_part, dim3((unsigned)((H + 63) / 64), (unsigned)slices), dim3(64), 0, s, rows, H, X,
-                       rps, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return sum_slices(H, slices, part, (size_t)H, out, false, s);
 }
 
 // head: z_v = h_v . wo + bo, mu_v = tanh(z_v); one wave per variable
@@ -325,10 +328,12 @@ hipError_t head(int n, int H, const float *hv, const float *wo, const float *bo,
     return hipGetLastError();
 }
 
-// head backward and loss: dz_v = 2 (mu - t) / n * (1 - mu^2), dH_v = dz_v wo,
-// loss terms (mu - t)^2 / n and dz into per-variable buffers.
+// head backward and loss: dz_v = 2 (mu - t) / n * (1 - mu^2), dZ_v = dz_v wo
+// through the last layer's ReLU (y its output), loss terms (mu - t)^2 / n and
+// dz into per-variable buffers.
 __global__ void k_head_back(int n, int H, const float *__restrict__ mu, const float *__restrict__ t,
-                            const float *__restrict__ wo, float *dz, float *lterm, float *dH)
+                            const float *__restrict__ wo, const float *__restrict__ y, float *dz, float *lterm,
+                            float *dZ)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)n * H) return;
@@ -336,45 +341,64 @@ __global__ void k_head_back(int n, int H, const float *__restrict__ mu, const fl
     const int f = (int)(i - (int64_t)v * H);
     const float d = mu[v] - t[v];
     const float g = 2.f * d / (float)n * (1.f - mu[v] * mu[v]);
-    dH[i] = g * wo[f];
+    dZ[i] = y[i] > 0.f ? g * wo[f] : 0.f;
     if (f == 0) {
         dz[v] = g;
         lterm[v] = d * d / (float)n;
     }
 }
 
-hipError_t head_back(int n, int H, const float *mu, const float *t, const float *wo, float *dz, float *lterm,
-                     float *dH, hipStream_t s)
+hipError_t head_back(int n, int H, const float *mu, const float *t, const float *wo, const float *y, float *dz,
+                     float *lterm, float *dZ, hipStream_t s)
 {
     const int64_t total = (int64_t)n * H;
-    hipLaunchKernelGGL(k_head_back, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, n, H, mu, t, wo, dz,
-                       lterm, dH);
+    hipLaunchKernelGGL(k_head_back, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, n, H, mu, t, wo, y,
+                       dz, lterm, dZ);
     return hipGetLastError();
 }
 
-// dwo[f] = sum_v dz_v h_v[f] over fixed variable slices (partials)
-__global__ void k_dwo_part(int n, int H, const float *__restrict__ dz, const float *__restrict__ hv, int per,
-                           float *part)
+// Sums over the variables, partials per slice of `per` variables: column f < H
+// dz_v h_v[f] (the head's weights), column H dz_v (its bias), column H + 1 the
+// loss terms.  A block's four waves take a quarter of the slice each and add
+// their partials in wave order (one wave per slice of 256 variables took 57 us
+// at 2000 variables, bound by its chain of loads; 5 us so).
+__global__ __launch_bounds__(256) void k_head_sums(int n, int H, const float *__restrict__ dz,
+                                                   const float *__restrict__ lterm, const float *__restrict__ hv, int per,
+                                                   float *part)
 {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f > H) return;
+    __shared__ float sm[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int f = blockIdx.x * 64 + lane;
     const int v0 = blockIdx.y * per, v1 = min(n, v0 + per);
+    const int q = (per + 3) / 4;
+    const int a = v0 + wave * q, b = min(v1, a + q);
     float acc = 0.f;
-    for (int v = v0; v < v1; ++v) acc += dz[v] * (f < H ? hv[(size_t)v * H + f] : 1.f);
-    part[(size_t)blockIdx.y * (H + 1) + f] = acc;
+    if (f < H) {
+#pragma unroll 8
+        for (int v = a; v < b; ++v) acc += dz[v] * hv[(size_t)v * H + f];
+    } else if (f < H + 2) {
+        const float *p = f == H ? dz : lterm;
+#pragma unroll 8
+        for (int v = a; v < b; ++v) acc += p[v];
+    }
+    sm[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0 && f < H + 2)
+        part[(size_t)blockIdx.y * (H + 2) + f] = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
 }
 
-hipError_t dwo(int n, int H, const float *dz, const float *hv, float *part, int max_slices, float *out,
-               hipStream_t s)
+// out[0..H] = gradients of the head's weights and bias, *loss (optional)
+hipError_t head_sums(int n, int H, const float *dz, const float *lterm, const float *hv, float *part, float *out,
+                     float *loss, hipStream_t s)
 {
-    int slices = std::max(1, std::min(max_slices, (n + 255) / 256));
+    int slices = std::max(1, std::min(HEAD_SLICES, (n + 31) / 32));
     const int per = (n + slices - 1) / slices;
     slices = std::max(1, (n + per - 1) / per);
-    hipLaunchKernelGGL(k_dwo_part, dim3((unsigned)((H + 1 + 63) / 64), (unsigned)slices), dim3(64), 0, s, n, H, dz,
+    hipLaunchKernelGGL(k_head_sums, dim3((unsigned)((H + 2 + 63) / 64), (unsigned)slices), dim3(256), 0, s, n, H, dz, lterm,
                        hv, per, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sum_slices(H + 1, slices, part, (size_t)(H + 1), out, false, s);
+    return sum_slices(H + 1, slices, part, (size_t)(H + 2), out, s, loss ? 1 : 0, loss);
 }
 
 // Adam (Kingma & Ba 2015) on FP32 master weights; step t starts at 1.
@@ -443,23 +467,6 @@ hipError_t fill_f32(int64_t n, float *p, float v, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_fill_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, p, v);
-    return hipGetLastError();
-}
-
-// dst[r][f] = X[r][f] for f < H (first H columns of a rows x xstride matrix)
-__global__ void k_take_cols(int64_t total, int H, const float *__restrict__ X, int xstride, float *dst)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int64_t r = i / H;
-    dst[i] = X[(size_t)r * xstride + (i - r * H)];
-}
-
-hipError_t take_cols(int rows, int H, const float *X, int xstride, float *dst, hipStream_t s)
-{
-    const int64_t total = (int64_t)rows * H;
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_take_cols, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, total, H, X, xstride, dst);
     return hipGetLastError();
 }
 

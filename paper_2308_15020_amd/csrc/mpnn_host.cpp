@@ -117,8 +117,8 @@ ffsat_status ensure_ws(ffsat_mpnn *net, int n, int m)
         (st = get(N * H, &net->dHv)) || (st = get(Mc * H, &net->dHc)) || (st = get(N * 3 * H, &net->dXv)) ||
         (st = get(Mc * 3 * H, &net->dXc)))
         return st;
-    net->part_len = (size_t)64 * 3 * H * H;
-    if ((st = get(net->part_len, &net->part)) || (st = get((size_t)1024 * (H + 1), &net->cpart))) return st;
+    net->part_len = (size_t)64 * (3 * H + 1) * H;
+    if ((st = get(net->part_len, &net->part)) || (st = get((size_t)HEAD_SLICES * (H + 2), &net->cpart))) return st;
     net->cap_n = n;
     net->cap_m = m;
     return FFSAT_OK;
@@ -156,8 +156,8 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
     }
     const int n = p->n, m = p->m;
     const int nnz = (int)p->nnz;
-    std::vector<int32_t> cptr(m + 1), lit(nnz), vof(nnz), cof(nnz), vptr(n + 1, 0), vsl(nnz);
-    std::vector<float> wk(nnz), wd(nnz), fv((size_t)n * 8, 0.f), fc((size_t)m * 8, 0.f);
+    std::vector<int32_t> cptr(m + 1), lit(nnz), vof(nnz), vptr(n + 1, 0), vlit(nnz), vcon(nnz);
+    std::vector<float> wk(nnz), wd(nnz), vwk(nnz), vwd(nnz), fv((size_t)n * 8, 0.f), fc((size_t)m * 8, 0.f);
     std::vector<int> P(n, 0), Nn(n, 0);
     for (int c = 0; c <= m; ++c) cptr[c] = (int32_t)p->h_con_ptr[c];
     for (int c = 0; c < m; ++c) {
@@ -167,7 +167,6 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
             const int v = (l > 0 ? l : -l) - 1;
             lit[e] = v | (l < 0 ? (int32_t)0x80000000u : 0);
             vof[e] = v;
-            cof[e] = c;
             wk[e] = 1.0f / (float)k;
             if (l > 0) P[v]++; else Nn[v]++;
             vptr[v + 1]++;
@@ -184,14 +183,16 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
         f[6] = kind == FFSAT_KIND_XOR ? (float)(prm & 1) : 0.f;
     }
     for (int v = 0; v < n; ++v) vptr[v + 1] += vptr[v];
-    {
-        std::vector<int32_t> fill(vptr.begin(), vptr.end() - 1);
-        for (int e = 0; e < nnz; ++e) vsl[fill[vof[e]]++] = e;
-    }
-    for (int e = 0; e < nnz; ++e) {
-        const int v = vof[e];
-        wd[e] = 1.0f / (float)std::max(1, P[v] + Nn[v]);
-    }
+    std::vector<int32_t> fill(vptr.begin(), vptr.end() - 1);
+    for (int c = 0; c < m; ++c)
+        for (int e = cptr[c]; e < cptr[c + 1]; ++e) {
+            const int v = vof[e], q = fill[v]++;
+            wd[e] = 1.0f / (float)std::max(1, P[v] + Nn[v]);
+            vlit[q] = lit[e];
+            vcon[q] = c;
+            vwk[q] = wk[e];
+            vwd[q] = wd[e];
+        }
     for (int v = 0; v < n; ++v) {
         float *f = &fv[(size_t)v * 8];
         f[0] = 1.f;
@@ -202,8 +203,9 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
     MpnnGraph *g = new MpnnGraph();
     g->n = n; g->m = m; g->nnz = nnz;
     Packer pk;
-    pk.add(&g->con_ptr, cptr); pk.add(&g->lit, lit); pk.add(&g->var_of, vof); pk.add(&g->con_of, cof);
-    pk.add(&g->vptr, vptr); pk.add(&g->vslots, vsl); pk.add(&g->wk, wk); pk.add(&g->wd, wd);
+    pk.add(&g->con_ptr, cptr); pk.add(&g->lit, lit); pk.add(&g->var_of, vof);
+    pk.add(&g->wk, wk); pk.add(&g->wd, wd); pk.add(&g->vptr, vptr); pk.add(&g->vlit, vlit);
+    pk.add(&g->vcon, vcon); pk.add(&g->vwk, vwk); pk.add(&g->vwd, vwd);
     pk.add(&g->fv, fv); pk.add(&g->fc, fc);
     const ffsat_status st = pk.upload(&g->buf);
     if (st != FFSAT_OK) {
@@ -215,19 +217,24 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
     return FFSAT_OK;
 }
 
-int splits_for(int K) { return std::max(1, std::min(64, (K + 511) / 512)); }
+// Slices of a weight gradient's product over K rows: 128 rows each (two rounds
+// of loads per wave) up to 64 slices, the size of the partials' buffer.
+int splits_for(int K) { return std::max(1, std::min(64, (K + 127) / 128)); }
 
-// dW (K x H) = X^T dZ over `rows` rows, split over the rows, fixed-order sum
+// dW (K x H) = X^T dZ over `rows` rows and the bias gradient (column sums of
+// dZ, which follow dW in the parameter order), split over the rows,
+// fixed-order sum
 hipError_t weight_grad(ffsat_mpnn *net, int rows, int K, const float *X, int ldx, const float *dZ, float *out,
                        hipStream_t s)
 {
     const int H = net->H;
     int S = splits_for(rows);
-    while ((size_t)S * K * H > net->part_len && S > 1) S /= 2;
-    hipError_t e = gemm(true, false, 0, K, H, rows, X, ldx, dZ, H, net->part, H, nullptr, S, (size_t)K * H, s);
+    const size_t len = (size_t)(K + 1) * H;
+    while ((size_t)S * len > net->part_len && S > 1) S /= 2;
+    hipError_t e = gemm(true, false, 0, K, H, rows, X, ldx, dZ, H, net->part, H, nullptr, S, len, s, true);
     if (e != hipSuccess) return e;
     // exactly the slices the product wrote
-    return sum_slices((int64_t)K * H, gemm_slices(rows, S), net->part, (size_t)K * H, out, false, s);
+    return sum_slices((int64_t)len, gemm_slices(rows, S), net->part, len, out, s);
 }
 
 ffsat_status forward(ffsat_mpnn *net, MpnnGraph *g, hipStream_t s)
@@ -240,13 +247,11 @@ ffsat_status forward(ffsat_mpnn *net, MpnnGraph *g, hipStream_t s)
     const float *hv = net->hv0, *hc = net->hc0;
     for (int r = 0; r < net->R; ++r) {
         // messages into columns H..3H of X, the constraint's own state into 0..H
-        MCHK(gather(m, H, g->con_ptr, nullptr, g->var_of, g->lit, g->wk, hv, H, 0, 0, net->Xc[r], 3 * H, H, 2 * H, 0, s,
-                    hc));
+        MCHK(gather(0, m, H, g->con_ptr, g->var_of, g->lit, g->wk, hv, H, net->Xc[r], 3 * H, hc, H, nullptr, s));
         MCHK(gemm(false, false, 1, m, H, 3 * H, net->Xc[r], 3 * H, W + o[p_wc(r)], H, net->Hc[r], H, W + o[p_bc(r)], 1,
                   0, s));
         hc = net->Hc[r];
-        MCHK(gather(n, H, g->vptr, g->vslots, g->con_of, g->lit, g->wd, hc, H, 0, 0, net->Xv[r], 3 * H, H, 2 * H, 0, s,
-                    hv));
+        MCHK(gather(0, n, H, g->vptr, g->vcon, g->vlit, g->vwd, hc, H, net->Xv[r], 3 * H, hv, H, nullptr, s));
         MCHK(gemm(false, false, 1, n, H, 3 * H, net->Xv[r], 3 * H, W + o[p_wv(r)], H, net->Hv[r], H, W + o[p_bv(r)], 1,
                   0, s));
         hv = net->Hv[r];
@@ -261,32 +266,24 @@ ffsat_status backward(ffsat_mpnn *net, MpnnGraph *g, const float *target, float 
     const float *W = net->w;
     float *G = net->g;
     const auto &o = net->off;
-    MCHK(head_back(n, H, net->mu, target, W + o[p_wo(R)], net->dz, net->lterm, net->dHv, s));
-    MCHK(dwo(n, H, net->dz, net->Hv[R - 1], net->cpart, 1024, G + o[p_wo(R)], s));   // wo then bo
-    if (loss) MCHK(colsum(n, 1, net->lterm, net->cpart, 1024, loss, s));
-    MCHK(fill_f32((int64_t)m * H, net->dHc, 0.f, s));
+    // dHv, dHc hold each layer's gradient already taken back through its ReLU:
+    // the kernels that produce it read the layer's output and the own columns
+    // of the product above in place
+    MCHK(head_back(n, H, net->mu, target, W + o[p_wo(R)], net->Hv[R - 1], net->dz, net->lterm, net->dHv, s));
+    MCHK(head_sums(n, H, net->dz, net->lterm, net->Hv[R - 1], net->cpart, G + o[p_wo(R)], loss, s));   // wo then bo
     for (int r = R - 1; r >= 0; --r) {
-        MCHK(relu_back(n, H, net->dHv, net->Hv[r], nullptr, 0, s));
         MCHK(weight_grad(net, n, 3 * H, net->Xv[r], 3 * H, net->dHv, G + o[p_wv(r)], s));
-        MCHK(colsum(n, H, net->dHv, net->cpart, 1024, G + o[p_bv(r)], s));
         MCHK(gemm(false, true, 0, n, 3 * H, H, net->dHv, H, W + o[p_wv(r)], H, net->dXv, 3 * H, nullptr, 1, 0, s));
-        MCHK(take_cols(n, H, net->dXv, 3 * H, net->dHv, s));
-        MCHK(gather(m, H, g->con_ptr, nullptr, g->var_of, g->lit, g->wd, net->dXv, 3 * H, H, 2 * H, net->dHc, H, 0, 0,
-                    1, s));
-        MCHK(relu_back(m, H, net->dHc, net->Hc[r], nullptr, 0, s));
+        MCHK(gather(1, m, H, g->con_ptr, g->var_of, g->lit, g->wd, net->dXv, 3 * H, net->dHc, H,
+                    r == R - 1 ? nullptr : net->dXc, 3 * H, net->Hc[r], s));
         MCHK(weight_grad(net, m, 3 * H, net->Xc[r], 3 * H, net->dHc, G + o[p_wc(r)], s));
-        MCHK(colsum(m, H, net->dHc, net->cpart, 1024, G + o[p_bc(r)], s));
         MCHK(gemm(false, true, 0, m, 3 * H, H, net->dHc, H, W + o[p_wc(r)], H, net->dXc, 3 * H, nullptr, 1, 0, s));
-        MCHK(take_cols(m, H, net->dXc, 3 * H, net->dHc, s));
-        MCHK(gather(n, H, g->vptr, g->vslots, g->con_of, g->lit, g->wk, net->dXc, 3 * H, H, 2 * H, net->dHv, H, 0, 0,
-                    1, s));
+        MCHK(gather(1, n, H, g->vptr, g->vcon, g->vlit, g->vwk, net->dXc, 3 * H, net->dHv, H, net->dXv, 3 * H,
+                    r > 0 ? net->Hv[r - 1] : net->hv0, s));
     }
-    MCHK(relu_back(n, H, net->dHv, net->hv0, nullptr, 0, s));
     MCHK(weight_grad(net, n, 8, g->fv, 8, net->dHv, G + o[P_EV], s));
-    MCHK(colsum(n, H, net->dHv, net->cpart, 1024, G + o[P_EVB], s));
-    MCHK(relu_back(m, H, net->dHc, net->hc0, nullptr, 0, s));
+    MCHK(relu_back(m, H, net->dHc, net->hc0, net->dXc, 3 * H, s));
     MCHK(weight_grad(net, m, 8, g->fc, 8, net->dHc, G + o[P_EC], s));
-    MCHK(colsum(m, H, net->dHc, net->cpart, 1024, G + o[P_ECB], s));
     return FFSAT_OK;
 }
 

@@ -295,11 +295,11 @@ def measure(name, args, dev, headline):
             # pulled gradient: the other literals of every pulled occurrence
             # gathered, the remaining slots read, the entry lists read once per
             # 64 * rpl restarts, x read and the stepped x written, one objective
-            # and one count row per chunk written
-            rpl = 4 if B > 192 else (2 if B > 64 else 1)
+            # and one count row per block written
+            rpl = desc["pull_rpl"]
             nbytes = (4.0 * desc["pull_gathers_per_restart"] * B + 4.0 * desc["pull_other_slots"] * B
                       + desc["pull_entries"] * desc["pull_entry_bytes"] * math.ceil(B / (64 * rpl))
-                      + 8.0 * inst.n_vars * B + 8.0 * desc["pull_chunks"] * B)
+                      + 8.0 * inst.n_vars * B + 8.0 * desc["pull_rows"] * B)
             ent = roofline_entry(f"pulled gradient + projected step (transform-free constraints of length <= "
                                  f"{desc['pull']}: {desc['pull_entries']} occurrences, "
                                  f"{desc['pull_gathers_per_restart']} gathers per restart; "

@@ -1446,6 +1446,7 @@ static hipError_t enqueue_bins(ffsat_plan *pl, int io, EvalArgs<IO> a, hipStream
 {
     const Layout &Ly = pl->p->lay[io];
     const std::vector<Bin> &bins = pl->bins[io];
+    if (!bins.empty() && bins[0].pk >= pk_limit) return hipSuccess;   // every bin is pulled
     if constexpr (sizeof(IO) == 4) {
         if (pl->grouped && (pl->gblocks > 0 || pl->gblocks64 > 0)) {
             // the FP64 group on a side stream; the bins without a grouped
@@ -1715,11 +1716,34 @@ static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *c
                              const float *eta_dev = nullptr, const int32_t *skip = nullptr,
                              float *x_next = nullptr);
 
+// Tiling of k_pull: one variable per wave (a wave's variables follow one
+// another, four dependent loads each), two from 32768 variables on, and up to
+// four blocks of 64 restarts (an entry is decoded once for all of them), fewer
+// where that leaves the chip less than four waves per SIMD.  3-SAT at ratio
+// 4.2, us per step with 1 / 2 / 8 variables: n = 250, 1024 restarts 14 / 17 / 37;
+// n = 10000, 256 restarts 44 / 49 / 78; n = 100000, 256 restarts 396 / 388 / 414.
+static void pull_tiling(int n, int B, int vc_fixed, int *vc, int *rpl)
+{
+    *vc = vc_fixed > 0 ? vc_fixed : (n >= 32768 ? 2 : 1);
+    *rpl = B > 192 ? 4 : (B > 64 ? 2 : 1);
+    while (*rpl > 1 && (int64_t)((n + *vc - 1) / *vc) * ((B + 64 * *rpl - 1) / (64 * *rpl)) < 4096) *rpl /= 2;
+}
+
+// Pull class that takes every constraint of the plan (transform-free, at most
+// seven literals), PULL_OFF if some constraint has none.
+static int pull_all_class(const ffsat_plan *pl)
+{
+    int c = PULL_LE3;
+    for (const Bin &b : pl->bins[IO_F32]) c = std::min(c, b.pk);
+    return pl->bins[IO_F32].empty() ? PULL_OFF : c;
+}
+
 // Switches the pull path to class c (PULL_OFF, PULL_LE7, PULL_LE3): builds
 // the problem's entry lists for c on first use and the plan's second point
 // buffer.  A class without pullable bins, or the grouped launch of every
-// bin (which holds the transform-free bins), turns it off; PULL_LE7 without
-// constraints of length 4..7 is PULL_LE3.  Changing the class drops the
+// bin (which holds the transform-free bins; unless the class takes them all
+// and the structure is automatic: then nothing is left to launch), turns it
+// off; PULL_LE7 without constraints of length 4..7 is PULL_LE3.  Changing the class drops the
 // cached graphs.
 static ffsat_status set_pull(ffsat_plan *pl, int c)
 {
@@ -1733,7 +1757,8 @@ static ffsat_status set_pull(ffsat_plan *pl, int c)
         for (const Bin &b : pl->bins[IO_F32]) any = any || b.pk >= c;
         // k_pull's gathers are buffer loads with 31-bit offsets into x
         const bool fits = (int64_t)pl->p->n * pl->B * 4 <= 0x7fffffffll;
-        if (!any || !fits || pl->mode == MODE_GROUP_ALL) c = PULL_OFF;
+        const bool held = pl->mode == MODE_GROUP_ALL && !(pl->mode_auto && pull_all_class(pl) >= c);
+        if (!any || !fits || held) c = PULL_OFF;
     }
     if (c != PULL_OFF) {
         ffsat_status st = build_pull(pl->p, c);
@@ -2012,7 +2037,7 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
     }
     pl->persistent = persist == 1;
     pl->pull_auto = preq == 0;
-    pl->pull_vc = vc > 0 ? vc : 8;
+    pull_tiling(p->n, B, vc, &pl->pull_vc, &pl->pull_rpl);
     default_shapes(pl);
     pl->use_graphs = opts ? opts->use_graphs != 0 : true;
     if (opts && opts->tune_cache) pl->tune_cache = opts->tune_cache;
@@ -2038,6 +2063,12 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
             if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
         if (e != hipSuccess) st = fail(FFSAT_E_HIP, "side streams: %s", hipGetErrorString(e));
     }
+    // every constraint of at most three literals: gathered from the start, one
+    // launch a step instead of two and no slots (3-SAT, n = 250 at 1024 restarts 22
+    // -> 14 us per step, n = 10000 at 256 88 -> 44, n = 100000 at 256 1030 -> 480).
+    // Longer ones gather k - 1 points per literal and do not always win (OR of
+    // 3..7, n = 2000: 31 -> 36 us at 256 restarts, 90 -> 74 at 1024): the tuner's choice.
+    if (st == FFSAT_OK && pl->pull_auto && pl->mode_auto && pull_all_class(pl) == PULL_LE3) st = set_pull(pl, PULL_LE3);
     if (st == FFSAT_OK && !pl->pull_auto) st = set_pull(pl, preq == 1 ? PULL_OFF : (preq == 2 ? PULL_LE7 : PULL_LE3));
     if (st == FFSAT_OK && pl->persistent) {
         // eligible: every constraint pulled (transform-free, length <= 7) and
@@ -2158,6 +2189,7 @@ extern "C" ffsat_status ffsat_plan_destroy(ffsat_plan *pl)
 }
 
 static int eval_rows(const ffsat_plan *pl, int io, int pull);
+static int pull_rows(const ffsat_plan *pl);
 
 extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, size_t len)
 {
@@ -2174,7 +2206,7 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
       << ", \"pull_entry_bytes\": " << (pl->pull ? 4 * PULL_E[pl->pull] : 0)
       << ", \"pull_gathers_per_restart\": " << (pl->pull ? pl->p->lay[IO_F32].pull[pl->pull].n_gather : 0)
       << ", \"pull_other_slots\": " << (pl->pull ? pl->p->lay[IO_F32].pull[pl->pull].n_rest : 0)
-      << ", \"pull_chunks\": " << (pl->pull ? (pl->p->n + pl->pull_vc - 1) / pl->pull_vc : 0)
+      << ", \"pull_rows\": " << (pl->pull ? pull_rows(pl) : 0) << ", \"pull_rpl\": " << pl->pull_rpl
       << ", \"objective_rows\": " << eval_rows(pl, IO_F32, pl->pull)
       << ", \"group_real_cpw\": " << pl->group_real_cpw << ", \"group_dft_fg\": " << pl->group_dft_fg
       << ", \"tuned_modes\": [" << pl->tune_log << "], \"persistent_steps\": "
@@ -2233,14 +2265,21 @@ static bool pull_on(const ffsat_plan *pl, int io, const void *con_val, bool grad
     return io == IO_F32 && pl->pull > 0 && con_val == nullptr && grad_or_step;
 }
 
+// Objective / count rows of k_pull: one per block of four chunks of variables.
+static int pull_rows(const ffsat_plan *pl)
+{
+    const int chunks = (pl->p->n + pl->pull_vc - 1) / pl->pull_vc;
+    return (chunks + PULL_WAVES - 1) / PULL_WAVES;
+}
+
 // Objective / count rows an evaluation writes: the launched bins' rows (the
-// first rows), then with the pull path one row per variable chunk.
+// first rows), then with the pull path those of k_pull.
 static int eval_rows(const ffsat_plan *pl, int io, int pull)
 {
     int rows = 0;
     for (const Bin &b : pl->bins[io])
         if (!pull || b.pk < pull) rows += (b.count + b.cpw - 1) / b.cpw;
-    if (pull) rows += (pl->p->n + pl->pull_vc - 1) / pl->pull_vc;
+    if (pull) rows += pull_rows(pl);
     return rows;
 }
 
@@ -2274,7 +2313,8 @@ static hipError_t enqueue_pull(ffsat_plan *pl, const float *x, float *grad, floa
     a.n = p->n;
     a.B = pl->B;
     a.vc = pl->pull_vc;
-    a.row0 = eval_rows(pl, IO_F32, pl->pull) - (p->n + pl->pull_vc - 1) / pl->pull_vc;
+    a.rpl = pl->pull_rpl;
+    a.row0 = eval_rows(pl, IO_F32, pl->pull) - pull_rows(pl);
     a.wm = (p->m + 31) / 32;
     a.want_check = want_check ? 1 : 0;
     a.rk = P.d_rk;

@@ -126,7 +126,8 @@ struct Bin {
 enum { PULL_OFF = 0, PULL_LE7 = 1, PULL_LE3 = 2 };
 constexpr int PULL_K[3] = {0, 7, 3};
 constexpr int PULL_E[3] = {0, 8, 4};
-constexpr int PULL_VC_MAX = 8;   // variables per wave of k_pull (its LDS holds their sums and points)
+constexpr int PULL_VC_MAX = 8;   // most variables per wave of k_pull
+constexpr int PULL_WAVES = 4;    // waves per block of k_pull, which share an objective / count row
 
 // Pulled occurrences of the constraints of pull class >= c, per variable.
 struct PullLayout {
@@ -317,6 +318,7 @@ struct ffsat_plan {
     int pull = 0;
     bool pull_auto = false;
     int pull_vc = 8;                 // variables per wave of k_pull
+    int pull_rpl = 4;                // 64-restart blocks per wave of k_pull
     bool persistent = false;         // ffsat_run_steps as one persistent launch (small all-pulled problems)
     int persistent_class = 0;        // the pull class whose entry lists it reads (0: not eligible)
     float *d_xalt = nullptr;         // [n][B] second point buffer of in-place pulled steps
@@ -379,7 +381,7 @@ hipError_t launch_reduce_f32(const ReduceArgs<float> &r, hipStream_t s);
 // plus the pulled occurrences' terms (entry order), summed in FP64; then
 // either the gradient or the projected step into x_out (never x).  The
 // objective term and the exact check of every pulled constraint are taken
-// at the entry of its first literal; one objective / count row per chunk.
+// at the entry of its first literal; one objective / count row per block.
 struct PullArgs {
     const float *x;
     float *x_out;             // projected step (x_out != x), or null
@@ -401,6 +403,7 @@ struct PullArgs {
     const float *rk;
     int64_t x_bytes;               // size of x (buffer-load bound, < 2^31)
     int n, B, vc, row0, wm, want_check;
+    int rpl;                       // 64-restart blocks per lane: 1, 2 or 4
 };
 constexpr int RK_TABLE = 40;
 hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s);

@@ -47,7 +47,7 @@ __device__ __forceinline__ float ldf(__amdgpu_buffer_rsrc_t r, int voff, unsigne
 // compiler reads the uniform ones (kind table, weights) through the scalar
 // cache.
 template <int E, int RPL, bool STEP>
-__global__ __launch_bounds__(256) void k_pull(PullArgs a, const float *__restrict__ rkt, const float *__restrict__ wts,
+__global__ __launch_bounds__(64 * PULL_WAVES) void k_pull(PullArgs a, const float *__restrict__ rkt, const float *__restrict__ wts,
                                               const int32_t *__restrict__ pent, const int32_t *__restrict__ pptr,
                                               const int32_t *__restrict__ vslot, const int32_t *__restrict__ vptr)
 {
@@ -56,10 +56,10 @@ __global__ __launch_bounds__(256) void k_pull(PullArgs a, const float *__restric
     constexpr int NS = 16 / RPL;                           // slots per batch
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int chunk = (int)blockIdx.x * 4 + wave;
-    const int n_chunks = (a.n + a.vc - 1) / a.vc;
-    if (chunk >= n_chunks) return;                   // whole wave
-    if (a.skip != nullptr && *a.skip == 0) return;   // uniform
+    __shared__ float fsum[PULL_WAVES][64 * RPL];
+    __shared__ int csum[PULL_WAVES][64 * RPL];
+    const int chunk = (int)blockIdx.x * PULL_WAVES + wave;
+    if (a.skip != nullptr && *a.skip == 0) return;   // uniform: the whole block leaves
     const unsigned bstride = (unsigned)a.B * 4u;     // bytes per variable row
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.x), (short)0,
                                                                           (int)a.x_bytes, BUF_DW3);
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void k_pull(PullArgs a, const float *__restric
         lo[r] = (bok[r] ? bl[r] : a.B - 1) * 4;
     }
     const int v0 = chunk * a.vc;
-    const int nv = min(a.vc, a.n - v0);
+    const int nv = min(a.vc, a.n - v0);   // <= 0 past the last variable: the wave only joins the sums
     const int pb = lane <= nv ? pptr[v0 + lane] : 0;
     const int sb = lane <= nv ? vptr[v0 + lane] : 0;
     float facc[RPL];
@@ -200,12 +200,26 @@ __global__ __launch_bounds__(256) void k_pull(PullArgs a, const float *__restric
             }
         }
     }
+    // the block's waves share a row, added in wave order
 #pragma unroll
     for (int r = 0; r < RPL; ++r) {
-        if (!bok[r]) continue;
-        const size_t rowi = (size_t)(a.row0 + chunk) * (size_t)a.B + (size_t)bl[r];
-        a.fpart[rowi] = facc[r];
-        if (a.want_check) a.cpart[rowi] = nuns[r];
+        fsum[wave][r * 64 + lane] = facc[r];
+        csum[wave][r * 64 + lane] = nuns[r];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * RPL; i += 64 * PULL_WAVES) {
+        const int b = (int)blockIdx.y * RPL * 64 + i;
+        if (b >= a.B) continue;
+        float f = fsum[0][i];
+        int c = csum[0][i];
+#pragma unroll
+        for (int w = 1; w < PULL_WAVES; ++w) {
+            f += fsum[w][i];
+            c += csum[w][i];
+        }
+        const size_t rowi = (size_t)(a.row0 + (int)blockIdx.x) * (size_t)a.B + (size_t)b;
+        a.fpart[rowi] = f;
+        if (a.want_check) a.cpart[rowi] = c;
     }
 }
 
@@ -213,11 +227,11 @@ template <int E, int RPL>
 static void launch_pull_t(const PullArgs &a, hipStream_t s)
 {
     const int chunks = (a.n + a.vc - 1) / a.vc;
-    const dim3 grid((unsigned)((chunks + 3) / 4), (unsigned)((a.B + 64 * RPL - 1) / (64 * RPL)));
+    const dim3 grid((unsigned)((chunks + PULL_WAVES - 1) / PULL_WAVES), (unsigned)((a.B + 64 * RPL - 1) / (64 * RPL)));
     if (a.x_out)
-        hipLaunchKernelGGL((k_pull<E, RPL, true>), grid, dim3(256), 0, s, a, a.rk, a.w, a.pent, a.pptr, a.vslot, a.vptr);
+        hipLaunchKernelGGL((k_pull<E, RPL, true>), grid, dim3(64 * PULL_WAVES), 0, s, a, a.rk, a.w, a.pent, a.pptr, a.vslot, a.vptr);
     else
-        hipLaunchKernelGGL((k_pull<E, RPL, false>), grid, dim3(256), 0, s, a, a.rk, a.w, a.pent, a.pptr, a.vslot, a.vptr);
+        hipLaunchKernelGGL((k_pull<E, RPL, false>), grid, dim3(64 * PULL_WAVES), 0, s, a, a.rk, a.w, a.pent, a.pptr, a.vslot, a.vptr);
 }
 
 hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s)
@@ -225,8 +239,8 @@ hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s)
     if (a.n <= 0 || a.B <= 0) return hipSuccess;
     if ((a.x_out == nullptr) == (a.grad == nullptr) || a.x_out == a.x) return hipErrorInvalidValue;
     if (a.vc < 1 || a.vc > PULL_VC_MAX || a.x_bytes > 0x7fffffffll) return hipErrorInvalidValue;
-    // restarts per lane: as many 64-blocks as the batch fills, up to 4
-    const int rpl = a.B > 192 ? 4 : (a.B > 64 ? 2 : 1);
+    const int rpl = a.rpl;
+    if (rpl != 1 && rpl != 2 && rpl != 4) return hipErrorInvalidValue;
     if (E == 4) {
         if (rpl == 4) launch_pull_t<4, 4>(a, s);
         else if (rpl == 2) launch_pull_t<4, 2>(a, s);

@@ -29,6 +29,7 @@ bool eval_variant_exists(int io, int ct, int cls, int seg, int L, bool uc)
 
 hipError_t launch_eval_bin_f32(const Bin &bin, const EvalArgs<float> &a, hipStream_t s)
 {
+    if (bin.cnt) return launch_count_bin(bin, a, s);
     if (bin.uc) return launch_fn<float>(pick_uc_f32(bin.ct, bin.seg, bin.L), bin, a, s);
     return launch_fn<float>(pick_f32(bin.ct, bin.cls, bin.seg, bin.L), bin, a, s);
 }

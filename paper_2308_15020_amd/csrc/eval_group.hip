@@ -5,14 +5,14 @@
 // with the memory-bound real-chain blocks spread among them.  One launch
 // keeps all CUs busy across bins of very different cost, with no
 // cross-stream synchronisation.
-#include "eval_kernel.h"
+#include "count_kernel.h"
 
 namespace ffsat {
 
 // Kernel variants of a grouped launch (FP32 arithmetic, the shapes of the
 // FP32 shape rule): (SEG, L) for L = 1 with SEG in {4, 8, ..., 24}, and for
 // L in {2, 4, 8, 16} with SEG in {16, 20, 24}; real chains first, then
-// root-of-unity products.
+// root-of-unity products, then the count form's shapes.
 #define FFSAT_GROUP_SHAPES(X, CPLX, BASE)                                                              \
     X(BASE + 0, 4, 1, CPLX) X(BASE + 1, 8, 1, CPLX) X(BASE + 2, 12, 1, CPLX) X(BASE + 3, 16, 1, CPLX)  \
     X(BASE + 4, 20, 1, CPLX) X(BASE + 5, 24, 1, CPLX) X(BASE + 6, 16, 2, CPLX) X(BASE + 7, 20, 2, CPLX) \
@@ -22,9 +22,16 @@ namespace ffsat {
     X(BASE + 17, 24, 16, CPLX)
 constexpr int GROUP_SHAPES = 18;
 
-int group_variant(int ct, int cls, int seg, int L)
+int group_variant(int ct, int cls, int seg, int L, bool cnt)
 {
     if (ct != CT_F32) return -1;
+    if (cnt) {
+#define X(ID, S, LL) \
+    if (seg == S && L == LL) return 2 * GROUP_SHAPES + ID;
+        FFSAT_COUNT_SHAPES(X)
+#undef X
+        return -1;
+    }
     const int base = cls == CLASS_DFT ? GROUP_SHAPES : 0;
 #define X(ID, S, LL, C) \
     if (seg == S && L == LL) return ID + base;
@@ -48,6 +55,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                                                     const int2 *__restrict__ blk)
 {
     extern __shared__ __align__(16) char group_lds[];
+    __shared__ float count_lds[4 * COUNT_LDS_MAX];   // 33 KB: four blocks a CU, as the registers allow
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int2 bw = blk[blockIdx.x];
     const GroupEntry e = ent[__builtin_amdgcn_readfirstlane(bw.x)];
@@ -62,6 +70,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         break;
         FFSAT_GROUP_SHAPES(X, false, 0)
         FFSAT_GROUP_SHAPES(X, true, GROUP_SHAPES)
+#undef X
+#define X(ID, S, LL)                                                                                     \
+    case 2 * GROUP_SHAPES + ID:                                                                          \
+        count_unit<S, LL>(a, sp, unit, xin, con, lits, wts, count_lds + wave * COUNT_LDS_MAX);           \
+        break;
+        FFSAT_COUNT_SHAPES(X)
 #undef X
     default: break;
     }

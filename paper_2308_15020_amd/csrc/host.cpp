@@ -586,6 +586,31 @@ void shape_for(int ct, int k, int &seg, int &L, bool dft)
     else seg = ((s + 7) / 8) * 8;   // 24 (32 only past k = 384)
 }
 
+// Segment shape of the count form (k <= COUNT_MAX_LEN): as few lanes as
+// reach with 16 literals each on one or two and 32 on four, since the work
+// above a lane's own literals grows with the lanes.
+void shape_for_count(int k, int &seg, int &L)
+{
+    L = k <= 16 ? 1 : (k <= 32 ? 2 : 4);
+    const int s = (k + L - 1) / L;
+    seg = L == 1 ? std::max(4, (s + 3) / 4 * 4) : (s <= 12 ? 12 : (s + 7) / 8 * 8);   // 4, 8, 12, 16; 12, 16; 12, 16, 24, 32
+}
+
+// Operations of one restart of a constraint in the count form (an FMA is
+// one), as the kernel runs it on L lanes of s literals.
+double count_ops(int s, int L)
+{
+    const int h = s <= 16 ? s : s / 2, halves = s / h;
+    auto poly = [](int n) { double o = 21.0 * (n / 4); for (int u = 4; u < n; u += 4) o += 5.0 * (u + 1); return o; };
+    double down = 0;   // seg_down of h literals
+    for (int u = 0; u < h; u += 4) down += 28.0 + (u ? poly(u) + 21.0 + 4.0 * (u + 1) + 5.0 * u : 0.0);
+    double ops = 8.0 * s + halves * poly(h) + halves * down;
+    if (halves == 2) ops += (h + 1.0) * (h + 1.0) + 2 * (poly(h) + h * (h + 1.0));
+    if (L == 2) ops += 4.0 * s;
+    if (L == 4) ops += (s + 1.0) * (s + 2.0) / 2 + s * (s + 1.0) + 14.0 * s;
+    return L * ops;
+}
+
 struct TypeKey {
     int cls, ct, kind, param, k, L, seg;
     bool operator<(const TypeKey &o) const
@@ -792,8 +817,9 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
     std::vector<Item> items((size_t)m);
     struct BinKey {
         int cls, ct, seg, L, pk;
+        bool cnt;
         bool operator<(const BinKey &o) const {
-            return std::tie(cls, ct, seg, L, pk) < std::tie(o.cls, o.ct, o.seg, o.L, o.pk);
+            return std::tie(cls, ct, seg, L, pk, cnt) < std::tie(o.cls, o.ct, o.seg, o.L, o.pk, o.cnt);
         }
     };
     std::vector<int8_t> rkind((size_t)m, -1);   // original order
@@ -813,22 +839,27 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
         int ct;
         if (io == IO_F64) ct = CT_F64;
         else ct = (cls == CLASS_DFT && k >= p->fp64_min_len) ? CT_F64 : CT_F32;
+        // at-least-t in FP32 up to COUNT_MAX_LEN literals: the count form
+        const bool cnt = cls == CLASS_DFT && ct == CT_F32 && kind == FFSAT_KIND_CARD_GE && !uc && !force_dft &&
+                         k <= COUNT_MAX_LEN;
         int seg, L;
         if (uc && cls == CLASS_DFT) shape_for_uc(k, seg, L);
+        else if (cnt) shape_for_count(k, seg, L);
         else shape_for(ct, k, seg, L, cls == CLASS_DFT);
-        if (!eval_variant_exists(io, ct, cls, seg, L, uc))
+        if (cnt ? !count_variant_exists(seg, L) : !eval_variant_exists(io, ct, cls, seg, L, uc))
             return fail(FFSAT_E_UNSUPPORTED, "no kernel variant for constraint %d (k=%d)", c, k);
         TypeKey tk;
         if (cls == CLASS_REAL) tk = TypeKey{cls, ct, rk, rparam, 0, 0, 0};
         else {
             int nprm = kind == FFSAT_KIND_XOR ? (prm & 1) : (kind == FFSAT_KIND_OR ? 0 : prm);
-            tk = TypeKey{cls, ct, kind, nprm, k, L, seg};
+            tk = cnt ? TypeKey{cls, ct, kind, 0, 0, 0, 0} : TypeKey{cls, ct, kind, nprm, k, L, seg};
         }
         auto it = type_index.find(tk);
         int ti;
         if (it == type_index.end()) {
             TypeD td;
-            if (cls == CLASS_DFT && ct == CT_F64 && !uc && kind != FFSAT_KIND_XOR && k >= NODE_MIN_LEN) {
+            if (cnt) td.cls = CLASS_DFT;   // the kernel takes t from the descriptor
+            else if (cls == CLASS_DFT && ct == CT_F64 && !uc && kind != FFSAT_KIND_XOR && k >= NODE_MIN_LEN) {
                 // at-least-t (OR: t = 1): frequencies chosen at the point
                 td.cls = CLASS_DFT;
                 td.thr = kind == FFSAT_KIND_OR ? 1 : prm;
@@ -860,20 +891,21 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
                                         : rk == RK_XOR ? (rparam ? RKIND_XOR_ODD : RKIND_XOR_EVEN)
                                         : (rparam < 0 ? RKIND_TRUE : RKIND_FALSE));
         }
-        BinKey bk{cls, ct, seg, L, pk};
+        BinKey bk{cls, ct, seg, L, pk, cnt};
         auto bi = bin_index.find(bk);
         int bidx;
         if (bi == bin_index.end()) {
             Bin b;
             b.cls = cls; b.ct = ct; b.seg = seg; b.L = L; b.pk = pk;
             b.uc = uc && cls == CLASS_DFT;
+            b.cnt = cnt;
             bidx = (int)bins.size();
             bins.push_back(b);
             bin_index[bk] = bidx;
         } else {
             bidx = bi->second;
         }
-        const double cost = cls == CLASS_DFT ? (double)k * (double)(types[ti].nf + 1) * 9.0
+        const double cost = cnt ? count_ops(seg, L) : cls == CLASS_DFT ? (double)k * (double)(types[ti].nf + 1) * 9.0
                                              : (double)k * 4.0;
         Bin &b = bins[(size_t)bidx];
         // Algorithmic work per restart.  Running products (FP32, and the
@@ -887,7 +919,10 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
         {
             const TypeD &td = types[(size_t)ti];
             const double nfc = (double)td.nf;
-            if (cls == CLASS_DFT && ct == CT_F64 && !uc) {
+            if (cnt) {
+                alg = 2.0 * count_ops(seg, L);
+                b.flops += alg;
+            } else if (cls == CLASS_DFT && ct == CT_F64 && !uc) {
                 alg = poly_flops(seg, L, td.nf);
                 b.flops += alg;
             } else {
@@ -1183,7 +1218,8 @@ static ffsat_status ensure_workspace(ffsat_plan *pl, int io)
 static std::string bin_key(const ffsat_plan *pl, const Bin &b, int io)
 {
     char buf[256];
-    snprintf(buf, sizeof buf, "gfx950|io%d|B%d|c%d%s|t%d|s%d|L%d|n%d|l%lld|k%d", io, pl->B, b.cls, b.uc ? "uc" : "",
+    snprintf(buf, sizeof buf, "gfx950|io%d|B%d|c%d%s|t%d|s%d|L%d|n%d|l%lld|k%d", io, pl->B, b.cls,
+             b.uc ? "uc" : (b.cnt ? "cnt" : ""),
              b.ct, b.seg, b.L, b.count, (long long)b.lits, b.maxk);
     return buf;
 }
@@ -1383,7 +1419,7 @@ static ffsat_status build_groups(ffsat_plan *pl)
             row0 += rows;
             continue;
         }
-        const int v = b.uc ? -1 : group_variant(b.ct, b.cls, b.seg, b.L);
+        const int v = b.uc ? -1 : group_variant(b.ct, b.cls, b.seg, b.L, b.cnt);
         const int fg = b.cls == CLASS_DFT ? b.fg : 1;
         if (v < 0 || (fg != 1 && fg != 4) || (pl->mode == MODE_GROUP_DFT && b.cls != CLASS_DFT)) {
             pl->gsolo.push_back(i);
@@ -1628,7 +1664,7 @@ constexpr int GROUP_CODE_MAX = 8 * 64 + 7;   // cache code of the grouped shapes
 static bool in_group(const ffsat_plan *pl, const Bin &b)
 {
     if (in_group64(b)) return true;
-    if (b.uc || group_variant(b.ct, b.cls, b.seg, b.L) < 0) return false;
+    if (b.uc || group_variant(b.ct, b.cls, b.seg, b.L, b.cnt) < 0) return false;
     return b.cls == CLASS_DFT || pl->mode == MODE_GROUP_ALL;
 }
 // Sets the group values (c: transform-free constraints per wave, all-bin
@@ -1654,7 +1690,7 @@ static void set_group_shapes(ffsat_plan *pl, int c, int f)
         if (b.cls == CLASS_REAL)
             b.cpw = g && c > 0 ? std::max(1, std::min({c, real_cpw_cap(b), b.count})) : pl->solo_cpw[i];
         else
-            b.fg = g && f > 0 ? f : pl->solo_fg[i];
+            b.fg = b.cnt ? 1 : (g && f > 0 ? f : pl->solo_fg[i]);   // the count form has no frequencies to split
     }
     pl->group_real_cpw = c;
     pl->group_dft_fg = f;
@@ -1673,6 +1709,7 @@ static void default_shapes(ffsat_plan *pl)
                 // one constraint per unit; split the frequencies over up to 4
                 // waves until the bin alone has about 3 waves per SIMD
                 b.cpw = 1;
+                if (b.cnt) continue;
                 if (pl->grouped) {
                     // the grouped launch fills the chip anyway: split the
                     // frequencies of long constraints only (fg 1 or 4)
@@ -1937,7 +1974,7 @@ extern "C" ffsat_status ffsat_plan_tune(ffsat_plan *pl, void *stream)
         if (hit != cache.end()) {
             b.cpw = hit->second.cpw;
             b.wpb = hit->second.wpb;
-            b.fg = b.cls == CLASS_DFT ? hit->second.fg : 1;
+            b.fg = b.cls == CLASS_DFT && !b.cnt ? hit->second.fg : 1;
             continue;
         }
         a.first = b.first;
@@ -1953,6 +1990,7 @@ extern "C" ffsat_status ffsat_plan_tune(ffsat_plan *pl, void *stream)
             for (int fg : {1, 2, 4})
                 for (int cpw : {1, 2, 4}) {
                     if (pl->grouped && fg == 2) break;   // grouped blocks take fg 1 or 4
+                    if (b.cnt && fg > 1) break;
                     if (cpw > 1 && cpw > b.count) break;
                     if (fg == 1) {
                         for (int wpb : {1, 2, 4}) cands.push_back({cpw, wpb, 1});
@@ -2215,7 +2253,7 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
         o << (io ? ", " : "") << "\"" << (io ? "f64" : "f32") << "\": [";
         for (size_t i = 0; i < pl->bins[io].size(); ++i) {
             const Bin &b = pl->bins[io][i];
-            o << (i ? ", " : "") << "{\"class\": \"" << (b.cls == CLASS_DFT ? (b.uc ? "dft_uc" : "dft") : "real") << "\", \"ct\": \""
+            o << (i ? ", " : "") << "{\"class\": \"" << (b.cls == CLASS_DFT ? (b.uc ? "dft_uc" : (b.cnt ? "count" : "dft")) : "real") << "\", \"ct\": \""
               << (b.ct == CT_F32 ? "f32" : "f64") << "\", \"seg\": " << b.seg << ", \"L\": " << b.L
               << ", \"first\": " << b.first << ", \"count\": " << b.count << ", \"maxk\": " << b.maxk
               << ", \"lits\": " << b.lits << ", \"cost\": " << b.cost << ", \"flops_per_restart\": " << b.flops

@@ -114,6 +114,7 @@ struct Bin {
     int cpw = 1, wpb = 4;       // tile shape: constraints per wave, waves per block
     int fg = 1;                 // root-of-unity bins: waves splitting one unit's frequencies
     bool uc = false;            // root-of-unity bin in the unit-circle form (ablation)
+    bool cnt = false;           // at-least-t bin in the count form (count_kernel.h; class DFT, FP32)
     int pk = 0;                 // pull class: 2 = transform-free, length <= 3; 1 = transform-free,
                                 // length 4..7; 0 = other (bins are ordered by pk, then cost)
 };
@@ -344,7 +345,10 @@ namespace ffsat {
 // kernels (eval.hip / aux.hip)
 hipError_t launch_eval_bin_f32(const Bin &bin, const EvalArgs<float> &a, hipStream_t s);
 hipError_t launch_eval_bin_f64(const Bin &bin, const EvalArgs<double> &a, hipStream_t s);
-int group_variant(int ct, int cls, int seg, int L);
+int group_variant(int ct, int cls, int seg, int L, bool cnt);
+constexpr int COUNT_MAX_LEN = 128;   // longest constraint of the count form
+bool count_variant_exists(int seg, int L);
+hipError_t launch_count_bin(const Bin &bin, const EvalArgs<float> &a, hipStream_t s);
 hipError_t launch_eval_group_f32(const EvalArgs<float> &a, const GroupEntry *ent, const int2 *blk, int nblk,
                                  size_t lds, hipStream_t s);
 // the long FP64-arithmetic root-of-unity bins of the FP32 evaluation

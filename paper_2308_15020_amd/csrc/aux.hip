@@ -462,27 +462,60 @@ __global__ __launch_bounds__(256) void k_fista_trial(int n, int B, int rows, int
     part[((size_t)chunks + blockIdx.y) * B + b] = sq;
 }
 
-// sufficient-decrease test per searching restart; partial sums in a fixed
-// order (FP64); on failure eta halves; after the last trial the point is
-// taken anyway.  pending counts the restarts still searching after this trial.
-__global__ void k_fista_accept(int B, int chunks, const float *__restrict__ part, const float *__restrict__ Fy,
-                               const float *__restrict__ Fz, float *eta, int32_t *searching, float *Fout, int last,
-                               int32_t *pending, const int32_t *__restrict__ skip)
+// Objective of the trial point and sufficient-decrease test per searching
+// restart: a block of 16 waves per 64 restarts; each wave adds a contiguous share
+// of the objective rows and of the trial's partial sums in order (FP64), wave 0
+// the waves' sums in wave order (fixed, deterministic).  On failure eta halves;
+// after the last trial the point is taken anyway.  pending counts the restarts
+// still searching after this trial.  One launch instead of the two levels of the
+// objective's sum and a test that walked the partial sums on one wave (65 us at
+// 2000 variables): a trial slot is three launches, which is all that an unneeded
+// one costs.
+static constexpr int ACCEPT_WAVES = 16;
+__global__ __launch_bounds__(64 * ACCEPT_WAVES) void k_fista_accept(int B, int frows, const float *__restrict__ fpart,
+                                                                    int chunks, const float *__restrict__ part,
+                                                                    const float *__restrict__ Fy, float *eta,
+                                                                    int32_t *searching, float *Fout, int last,
+                                                                    int32_t *pending, const int32_t *__restrict__ skip)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B || *skip == 0 || !searching[b]) return;
-    double dot = 0.0, sq = 0.0;
-    for (int c = 0; c < chunks; ++c) {
-        dot += (double)part[(size_t)c * B + b];
-        sq += (double)part[((size_t)chunks + c) * B + b];
+    __shared__ double sm[3][ACCEPT_WAVES][64];
+    if (*skip == 0) return;   // uniform: the whole block leaves
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int b = blockIdx.x * 64 + lane;
+    const bool on = b < B && searching[b] != 0;
+    const int bb = b < B ? b : B - 1;
+    double f = 0.0, dot = 0.0, sq = 0.0;
+    if (on) {
+        const int r0 = (int)((int64_t)frows * w / ACCEPT_WAVES), r1 = (int)((int64_t)frows * (w + 1) / ACCEPT_WAVES);
+#pragma unroll 16
+        for (int r = r0; r < r1; ++r) f += (double)fpart[(size_t)r * B + bb];
+        const int c0 = (int)((int64_t)chunks * w / ACCEPT_WAVES), c1 = (int)((int64_t)chunks * (w + 1) / ACCEPT_WAVES);
+#pragma unroll 8
+        for (int c = c0; c < c1; ++c) {
+            dot += (double)part[(size_t)c * B + bb];
+            sq += (double)part[((size_t)chunks + c) * B + bb];
+        }
     }
-    const float e = eta[b];
+    sm[0][w][lane] = f;
+    sm[1][w][lane] = dot;
+    sm[2][w][lane] = sq;
+    __syncthreads();
+    if (w != 0 || !on) return;
+    f = dot = sq = 0.0;
+#pragma unroll
+    for (int q = 0; q < ACCEPT_WAVES; ++q) {
+        f += sm[0][q][lane];
+        dot += sm[1][q][lane];
+        sq += sm[2][q][lane];
+    }
+    const float e = eta[b], Fz = (float)f;
     const double bound = (double)Fy[b] + dot + sq / (2.0 * (double)e);
-    const bool ok = (double)Fz[b] <= bound;
+    const bool ok = (double)Fz <= bound;
     if (!ok) eta[b] = 0.5f * e;
     if (ok || last) {
         searching[b] = 0;
-        if (Fout) Fout[b] = Fz[b];
+        if (Fout) Fout[b] = Fz;
     } else {
         atomicAdd(pending, 1);
     }
@@ -539,14 +572,14 @@ hipError_t launch_fista_trial(int n, int B, const float *y, const float *g, cons
     return hipGetLastError();
 }
 
-hipError_t launch_fista_accept(int n, int B, const float *part, const float *Fy, const float *Fz, float *eta,
+hipError_t launch_fista_accept(int n, int B, int frows, const float *fpart, const float *part, const float *Fy, float *eta,
                                int32_t *searching, float *Fout, int last, int32_t *pending, const int32_t *skip,
                                hipStream_t s)
 {
     const int rows = fista_rows(n, B);
     const int chunks = (n + rows - 1) / rows;
-    hipLaunchKernelGGL(k_fista_accept, dim3((B + 255) / 256), dim3(256), 0, s, B, chunks, part, Fy, Fz, eta, searching,
-                       Fout, last, pending, skip);
+    hipLaunchKernelGGL(k_fista_accept, dim3((B + 63) / 64), dim3(64 * ACCEPT_WAVES), 0, s, B, frows, fpart, chunks, part, Fy,
+                       eta, searching, Fout, last, pending, skip);
     return hipGetLastError();
 }
 

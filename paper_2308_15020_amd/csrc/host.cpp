@@ -2208,7 +2208,6 @@ extern "C" ffsat_status ffsat_plan_destroy(ffsat_plan *pl)
     (void)hipFree(pl->d_fz);
     (void)hipFree(pl->d_fg);
     (void)hipFree(pl->d_fFy);
-    (void)hipFree(pl->d_fFz);
     (void)hipFree(pl->d_fpartial);
     (void)hipFree(pl->d_fcoef);
     (void)hipFree(pl->d_fflags);
@@ -2850,15 +2849,19 @@ static ffsat_status ensure_fista(ffsat_plan *pl)
     HIPCHK(hipMalloc(&pl->d_fz, nb * sizeof(float)));
     HIPCHK(hipMalloc(&pl->d_fg, nb * sizeof(float)));
     HIPCHK(hipMalloc(&pl->d_fFy, B * sizeof(float)));
-    HIPCHK(hipMalloc(&pl->d_fFz, B * sizeof(float)));
     HIPCHK(hipMalloc(&pl->d_fpartial, 2 * chunks * B * sizeof(float)));
     HIPCHK(hipMalloc(&pl->d_fcoef, B * sizeof(float)));
     HIPCHK(hipMalloc(&pl->d_fflags, 2 * B * sizeof(int32_t)));
     HIPCHK(hipMalloc(&pl->d_fpending, (FISTA_MAX_LS + 1) * sizeof(int32_t)));
-    pl->device_bytes += (int64_t)((2 * nb + 2 * chunks * B + 3 * B) * sizeof(float) + 2 * B * sizeof(int32_t) +
+    pl->device_bytes += (int64_t)((2 * nb + 2 * chunks * B + 2 * B) * sizeof(float) + 2 * B * sizeof(int32_t) +
                                   (FISTA_MAX_LS + 1) * sizeof(int32_t));
     return FFSAT_OK;
 }
+
+// Objective rows that the acceptance test adds by itself; beyond, the first
+// level of the objective's sum runs before it (16 waves add 2048 rows in about 7
+// us, what the launch of that level costs).
+constexpr int FISTA_ROWS = 2048;
 
 // One FISTA iteration per restart (Alg. 5 with backtracking): gradient at y,
 // then max_ls trial slots.  A trial runs only while some restart is still
@@ -2882,10 +2885,21 @@ static hipError_t enqueue_fista_iter(ffsat_plan *pl, float *x, float *y, float *
         if ((e = launch_fista_trial(n, B, y, pl->d_fg, eta, searching, pl->d_fz, pl->d_fpartial, pending + q, s)) !=
             hipSuccess)
             return e;
-        if (run_eval<float>(pl, pl->d_fz, pl->d_fFz, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0.f, s,
-                            nullptr, pending + q) != FFSAT_OK)
-            return hipErrorUnknown;
-        if ((e = launch_fista_accept(n, B, pl->d_fpartial, pl->d_fFy, pl->d_fFz, eta, searching, F,
+        // the objective's rows at z; the test adds them
+        EvalArgs<float> a = base_args<float>(pl, IO_F32, pl->d_fz, nullptr, false);
+        a.skip = pending + q;
+        if ((e = enqueue_bins<float>(pl, IO_F32, a, s)) != hipSuccess) return e;
+        int rows = eval_rows(pl, IO_F32, 0);
+        const float *fpart = (const float *)pl->d_fpart[IO_F32];
+        if (rows > FISTA_ROWS) {
+            // F only asks for the rows' first level here
+            const ReduceArgs<float> r = reduce_args<float>(pl, IO_F32, nullptr, nullptr, 0.f, nullptr, pending + q,
+                                                           pl->d_fFy, nullptr, 0);
+            if ((e = launch_reduce_part_f32(r, 1, s)) != hipSuccess) return e;
+            fpart = (const float *)pl->d_ftmp[IO_F32];
+            rows = f_splits(rows);
+        }
+        if ((e = launch_fista_accept(n, B, rows, fpart, pl->d_fpartial, pl->d_fFy, eta, searching, F,
                                      q == max_ls - 1 ? 1 : 0, pending + q + 1, pending + q, s)) != hipSuccess)
             return e;
     }

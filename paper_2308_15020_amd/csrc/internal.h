@@ -279,9 +279,9 @@ struct ffsat_plan {
     int32_t *d_flag = nullptr;       // debug non-finite flag
     int32_t *d_umax = nullptr;       // [1024] partial maxima of the weight update
     float *d_scratch_x = nullptr;    // autotuner input
-    // FISTA workspace (allocated on first use): trial point, gradient at y,
-    // objective at y and at the trial, partial sums, flags, momentum, counter
-    float *d_fz = nullptr, *d_fg = nullptr, *d_fFy = nullptr, *d_fFz = nullptr, *d_fpartial = nullptr;
+    // FISTA workspace (allocated on first use): trial point, gradient and
+    // objective at y, partial sums, flags, momentum, counter
+    float *d_fz = nullptr, *d_fg = nullptr, *d_fFy = nullptr, *d_fpartial = nullptr;
     float *d_fcoef = nullptr;
     int32_t *d_fflags = nullptr, *d_fpending = nullptr;
     hipStream_t cap = nullptr;       // capture stream for graphs
@@ -495,7 +495,8 @@ hipError_t launch_fista_begin(int B, const float *eta, int32_t *active, int32_t 
                               hipStream_t s);
 hipError_t launch_fista_trial(int n, int B, const float *y, const float *g, const float *eta, const int32_t *searching,
                               float *z, float *part, const int32_t *skip, hipStream_t s);
-hipError_t launch_fista_accept(int n, int B, const float *part, const float *Fy, const float *Fz, float *eta,
+// objective of the trial point: the sum of the frows rows of fpart
+hipError_t launch_fista_accept(int n, int B, int frows, const float *fpart, const float *part, const float *Fy, float *eta,
                                int32_t *searching, float *Fout, int last, int32_t *pending, const int32_t *skip,
                                hipStream_t s);
 hipError_t launch_fista_finish(int n, int B, const int32_t *active, float *t, float *coef, const float *z, float *x,

@@ -294,10 +294,12 @@ struct ffsat_plan {
     int2 *d_gblk = nullptr;
     int gblocks = 0;
     size_t glds = 0;
-    ffsat::GroupEntry *d_gent64 = nullptr;   // the FP64 root-of-unity group (grouped structures)
-    int2 *d_gblk64 = nullptr;
-    int gblocks64 = 0;
-    size_t glds64 = 0;
+    // the FP64-arithmetic root-of-unity groups: of the FP32 evaluation (grouped
+    // structures) and of the FP64 evaluation (always)
+    ffsat::GroupEntry *d_gent64[2] = {nullptr, nullptr};
+    int2 *d_gblk64[2] = {nullptr, nullptr};
+    int gblocks64[2] = {0, 0};
+    size_t glds64[2] = {0, 0};
     std::vector<int> gsolo;          // bin indices launched on their own
     // three side streams: with the caller's stream, one per hardware queue
     // of HIP's default of four per process
@@ -351,8 +353,10 @@ bool count_variant_exists(int seg, int L);
 hipError_t launch_count_bin(const Bin &bin, const EvalArgs<float> &a, hipStream_t s);
 hipError_t launch_eval_group_f32(const EvalArgs<float> &a, const GroupEntry *ent, const int2 *blk, int nblk,
                                  size_t lds, hipStream_t s);
-// the long FP64-arithmetic root-of-unity bins of the FP32 evaluation
-int group_variant64(int seg, int L);
+// the root-of-unity bins with FP64 arithmetic of either evaluation
+int group_variant64(int io, int seg, int L);
+hipError_t launch_eval_group64_f64(const EvalArgs<double> &a, const GroupEntry *ent, const int2 *blk, int nblk,
+                                   size_t lds, hipStream_t s);
 hipError_t launch_eval_group64_f32(const EvalArgs<float> &a, const GroupEntry *ent, const int2 *blk, int nblk,
                                    size_t lds, hipStream_t s);
 bool eval_variant_exists(int io, int ct, int cls, int seg, int L, bool uc);

@@ -49,6 +49,11 @@ __device__ __forceinline__ float dpp_f32(float v)
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
+__device__ __forceinline__ int dpp_i32(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v)
 {
     const long long u = __double_as_longlong(v);
@@ -579,12 +584,12 @@ struct NodeWindow {
 template <int L>
 __device__ __forceinline__ NodeWindow node_window(float s1, float s, float mx, int k)
 {
-#pragma unroll
-    for (int d = 1; d < L; d <<= 1) {
-        s1 += __shfl_xor(s1, d, 64);
-        s += __shfl_xor(s, d, 64);
-        mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    }
+    // over the group's lanes: the butterfly of allreduce_prod_f64
+    if constexpr (L >= 2) { s1 += dpp_f32<0xB1>(s1); s += dpp_f32<0xB1>(s); mx = fmaxf(mx, dpp_f32<0xB1>(mx)); }
+    if constexpr (L >= 4) { s1 += dpp_f32<0x4E>(s1); s += dpp_f32<0x4E>(s); mx = fmaxf(mx, dpp_f32<0x4E>(mx)); }
+    if constexpr (L >= 8) { s1 += dpp_f32<0x141>(s1); s += dpp_f32<0x141>(s); mx = fmaxf(mx, dpp_f32<0x141>(mx)); }
+    if constexpr (L >= 16) { s1 += dpp_f32<0x140>(s1); s += dpp_f32<0x140>(s); mx = fmaxf(mx, dpp_f32<0x140>(mx)); }
+    static_assert(L <= 16, "groups of at most 16 lanes");
     int lo = 0, hi = k;
     float frac = 1.0f;
     if (mx <= 1.0f && s > -1.0f) {   // false for NaN
@@ -602,16 +607,20 @@ __device__ __forceinline__ NodeWindow node_window(float s1, float s, float mx, i
     }
     const float sm = s - 0.3f;   // one literal left out, and the sums' rounding
     if (2 * sm > NODE_B) frac = asinf(sqrtf(NODE_B / (2 * sm))) * 0.3183099f;
-#pragma unroll
-    for (int d = L; d < 64; d <<= 1) {
-        lo = min(lo, __shfl_xor(lo, d, 64));
-        hi = max(hi, __shfl_xor(hi, d, 64));
-        frac = fmaxf(frac, __shfl_xor(frac, d, 64));
-    }
+    // over the groups: within a row by rotations, the four rows on the scalar unit
+    // (frac > 0: its bits order as integers)
+    int fb = __float_as_int(frac);
+    if constexpr (L <= 1) { lo = min(lo, dpp_i32<0x121>(lo)); hi = max(hi, dpp_i32<0x121>(hi)); fb = max(fb, dpp_i32<0x121>(fb)); }
+    if constexpr (L <= 2) { lo = min(lo, dpp_i32<0x122>(lo)); hi = max(hi, dpp_i32<0x122>(hi)); fb = max(fb, dpp_i32<0x122>(fb)); }
+    if constexpr (L <= 4) { lo = min(lo, dpp_i32<0x124>(lo)); hi = max(hi, dpp_i32<0x124>(hi)); fb = max(fb, dpp_i32<0x124>(fb)); }
+    if constexpr (L <= 8) { lo = min(lo, dpp_i32<0x128>(lo)); hi = max(hi, dpp_i32<0x128>(hi)); fb = max(fb, dpp_i32<0x128>(fb)); }
     NodeWindow w;
-    w.lo = __builtin_amdgcn_readfirstlane(lo);
-    w.hi = __builtin_amdgcn_readfirstlane(hi);
-    w.frac = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(frac)));
+    w.lo = min(min(__builtin_amdgcn_readlane(lo, 0), __builtin_amdgcn_readlane(lo, 16)),
+               min(__builtin_amdgcn_readlane(lo, 32), __builtin_amdgcn_readlane(lo, 48)));
+    w.hi = max(max(__builtin_amdgcn_readlane(hi, 0), __builtin_amdgcn_readlane(hi, 16)),
+               max(__builtin_amdgcn_readlane(hi, 32), __builtin_amdgcn_readlane(hi, 48)));
+    w.frac = __int_as_float(max(max(__builtin_amdgcn_readlane(fb, 0), __builtin_amdgcn_readlane(fb, 16)),
+                                max(__builtin_amdgcn_readlane(fb, 32), __builtin_amdgcn_readlane(fb, 48))));
     return w;
 }
 // Frequencies whose coefficients a wave stages in LDS at a time (one per lane).

@@ -327,28 +327,17 @@ __device__ __forceinline__ void count_unit(const EvalArgs<float> &a, const Span 
     for (int ci = chunk * sp.cpw; ci < c_end; ++ci) {
         const ConDesc d = con[sp.first + ci];
         const int k = d.k;
-        int i0c = i0;
-        uint32_t one = 1u;
-        asm volatile("" : "+v"(i0c), "+v"(one));   // per-constraint copies (see eval_unit)
-        int nv = min(max(k - i0c, 0), S);
-        int lt[S];
-#pragma unroll
-        for (int i = 0; i < S; ++i) lt[i] = lits[d.off + min(i0c + i, k - 1)];
-        float p[S];
-#pragma unroll
-        for (int i = 0; i < S; ++i) p[i] = xin[(size_t)(lt[i] & 0x7fffffff) * a.B + bb];
-        // at least t true, or (t past the middle) fewer than t false
+        // at least t true, or (t past the middle) fewer than t false; p = 0 for padding
         const bool flip = 2 * d.chk > k + 1;
         const int t = flip ? k - d.chk + 1 : d.chk;
         const float half = flip ? 0.5f : -0.5f;
-        uint32_t negm = 0, tmask = 0;
+        float p[S];
+        int nv;
+        uint32_t negm, tmask;
+        load_segment<L, S, float>(a, d, xin, lits, i0, bb, flip ? -1.f : 1.f, p, nv, negm, tmask);
 #pragma unroll
-        for (int i = 0; i < S; ++i) {
-            const bool in = i < nv, neg = lt[i] < 0, vt = p[i] < 0.f;
-            negm |= ((in && neg) ? one : 0u) << i;
-            tmask |= ((in && (neg != vt)) ? one : 0u) << i;
-            p[i] = in ? __builtin_fmaf(neg ? -half : half, p[i], 0.5f) : 0.f;
-        }
+        for (int i = 0; i < S; ++i) p[i] = __builtin_fmaf(half, p[i], 0.5f);
+        float *const slot = a.slot + ((size_t)i0 * a.B + b);
         asm volatile("" : "+v"(negm));
         if (a.want_check) {
             const int cnt = group_sum_int<L>(__popc(tmask));
@@ -376,7 +365,7 @@ __device__ __forceinline__ void count_unit(const EvalArgs<float> &a, const Span 
             lane_down<S>(p, R, [&](int i, float g) {
                 if (i < nv && bok) {
                     const float gv = ((negm >> i) & 1u) ? -g : g;
-                    a.slot[(size_t)(d.off + i0 + i) * a.B + b] = wc * gv;
+                    slot[(size_t)(d.off + i) * a.B] = wc * gv;
                 }
             });
         }

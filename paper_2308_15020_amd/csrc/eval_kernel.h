@@ -377,6 +377,84 @@ __device__ __forceinline__ void freq_pass(const int j, const CT (&lv)[SEG], CT (
     }
 }
 
+// Step i input: the signed literal values of this lane's positions i0 .. i0 + SEG -
+// 1 of constraint d (pad past its end, position nv on), the sign of each (bit t
+// of negm) and its rounded truth (x_v < 0: True; bit t of tmask).  All literal
+// loads, then all point loads: two memory round trips per constraint.  On one
+// lane the literals are uniform (scalar loads, rows by scalar pointer); else a
+// lane reads its run of literals 16 bytes at a time (past the constraint's end the
+// next one's: the array has LIT_PAD entries of padding; the constraint's first
+// literal takes their place) and, where the points' bytes fit 32 bits
+// (a.x32), a point's offset is one 24-bit multiply-add.  Signs and truths are
+// gathered with shifts: as predicates they would hold a scalar pair per position
+// (63 instructions of spills to lanes per constraint at 20 positions over 16 lanes).
+// Against clamped single literal loads, 64-bit multiplies for every point and slot
+// and predicated signs: grouped FP64 launch of 1982 constraints of 128..512 literals,
+// 256 restarts 1465 -> 1387 us; of 1000, 150 settled points 381 -> 348; one step
+// of a mixed n = 2000 instance, 1024 restarts 1% less.
+template <int L, int SEG, typename IO>
+__device__ __forceinline__ void load_segment(const EvalArgs<IO> &a, const ConDesc &d, const IO *__restrict__ xin,
+                                             const int32_t *__restrict__ lits, const int i0, const int bb, const IO pad,
+                                             IO (&l)[SEG], int &nv, uint32_t &negm, uint32_t &tmask)
+{
+    static_assert(SEG <= 32, "one bit per position");
+    int lt[SEG];
+    if constexpr (L == 1) {
+        nv = min(d.k, SEG);
+#pragma unroll
+        for (int t = 0; t < SEG; ++t) lt[t] = lits[d.off + min(t, d.k - 1)];
+#pragma unroll
+        for (int t = 0; t < SEG; ++t)
+            l[t] = *reinterpret_cast<const IO *>(reinterpret_cast<const char *>(xin + (size_t)(lt[t] & 0x7fffffff) * a.B) +
+                                                 (unsigned)bb * (unsigned)sizeof(IO));
+    } else {
+        typedef int i4 __attribute__((ext_vector_type(4), aligned(4)));
+        // per-constraint copies the compiler cannot hoist
+        int i0c = i0;
+        asm volatile("" : "+v"(i0c));
+        nv = min(max(d.k - i0c, 0), SEG);
+        const int32_t *lp = lits + d.off + i0c;
+#pragma unroll
+        for (int t = 0; t + 4 <= SEG; t += 4) {
+            const i4 q = *reinterpret_cast<const i4 *>(lp + t);
+            lt[t] = q.x;
+            lt[t + 1] = q.y;
+            lt[t + 2] = q.z;
+            lt[t + 3] = q.w;
+        }
+#pragma unroll
+        for (int t = SEG / 4 * 4; t < SEG; ++t) lt[t] = lp[t];
+        const int first = lits[d.off];
+#pragma unroll
+        for (int t = 0; t < SEG; ++t) lt[t] = t < nv ? lt[t] : first;
+        if (a.x32) {
+            const unsigned rb = (unsigned)a.B * (unsigned)sizeof(IO), o = (unsigned)bb * (unsigned)sizeof(IO);
+#pragma unroll
+            for (int t = 0; t < SEG; ++t)   // the variable is below 2^24: the sign bit does not enter the product
+                l[t] = *reinterpret_cast<const IO *>(reinterpret_cast<const char *>(xin) + (__umul24((unsigned)lt[t], rb) + o));
+        } else {
+#pragma unroll
+            for (int t = 0; t < SEG; ++t) l[t] = xin[(size_t)(lt[t] & 0x7fffffff) * a.B + bb];
+        }
+        asm volatile("" : "+v"(nv));   // fresh comparisons below
+    }
+    uint32_t vm = 0;
+    negm = 0;
+#pragma unroll
+    for (int t = 0; t < SEG; ++t) {
+        const uint32_t sgn = (uint32_t)lt[t] & 0x80000000u;
+        negm |= ((uint32_t)lt[t] >> 31) << t;
+        vm |= (l[t] < IO(0) ? 1u : 0u) << t;
+        IO v;
+        if constexpr (sizeof(IO) == 4) v = __uint_as_float(__float_as_uint(l[t]) ^ sgn);
+        else v = __longlong_as_double(__double_as_longlong(l[t]) ^ ((long long)sgn << 32));
+        l[t] = t < nv ? v : pad;
+    }
+    const uint32_t in = nv >= 32 ? ~0u : (1u << nv) - 1u;
+    negm &= in;
+    tmask = (negm ^ vm) & in;
+}
+
 // ---- FP64 root-of-unity products in the polynomial form
 //
 // A lane's segment product of form-1 factors, init * prod_t (1 - i tau l_t),
@@ -573,9 +651,9 @@ __device__ __forceinline__ void seg_grad_from_moments(V (&v)[SEG], double (&H)[S
 // 4 (u^lo - u^t) / (N (1 - u)) gives c1 = r D, r = -2 C^(K-1) init^-L / N and
 // D = z^(K+1-2 lo) - z^(K+1-2 t), z = exp(i pi a / N).
 // Measured: large instance (1982 constraints of 128..512 literals, 256 restarts,
-// uniform points) grouped FP64 launch 4.62 -> 1.74 ms; 1000 such
+// uniform points) grouped FP64 launch 4.62 -> 1.39 ms (all else of it included); 1000 such
 // constraints at 150 points with four fifths of the variables at a face 1.52
-// -> 0.47 ms; error against 64 bits unchanged (FP64 evaluation 1.0e-15).
+// -> 0.35 ms; error against 64 bits unchanged (FP64 evaluation 1.0e-15).
 struct NodeWindow {
     int lo, hi;     // window of the count over the wave's restarts
     float frac;     // share of the circle's frequencies needed (>= 1/2: all)
@@ -722,39 +800,15 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
         const TypeT<CT> ty = types[d.type];
         const int k = d.k;
 
-        // step i input: this lane's SEG positions j*SEG .. j*SEG+SEG-1; the
-        // positions past the constraint's end hold the padding value (count
-        // neutral; its factor is divided out of the coefficients on the
-        // host).  Also the rounded truth of each literal (x_v < 0: True).
-        // Branch-free: all literal loads (indices clamped into the
-        // constraint), then all point loads, so that a lane waits for two
-        // memory round trips per constraint rather than two per position.
-        // kernels with long constraints: per-constraint copies the compiler cannot
-        // hoist; otherwise it keeps i0 + t and the bit constants 1 << t in
-        // SEG registers each across the whole kernel (real-chain kernels run
-        // many constraints per wave and profit from the hoisting)
-        int i0c = i0;
-        uint32_t one = 1u;
-        if constexpr (CPLX || L > 1) asm volatile("" : "+v"(i0c), "+v"(one));
-        int nv = min(max(k - i0c, 0), SEG);   // positions of this lane inside the constraint
-        int lt[SEG];
-#pragma unroll
-        for (int t = 0; t < SEG; ++t) lt[t] = lits[d.off + min(i0c + t, k - 1)];
-        IO xr[SEG];
-#pragma unroll
-        for (int t = 0; t < SEG; ++t) xr[t] = xin[(size_t)(lt[t] & 0x7fffffff) * a.B + bb];
+        IO xl[SEG];
+        int nv;
+        uint32_t negm, tmask;
+        load_segment<L, SEG, IO>(a, d, xin, lits, i0, bb, (IO)ty.pad, xl, nv, negm, tmask);
         CT lv[SEG];
-        uint32_t negm = 0, tmask = 0;
 #pragma unroll
-        for (int t = 0; t < SEG; ++t) {
-            const bool in = t < nv;
-            const bool neg = lt[t] < 0;
-            const CT xv = (CT)xr[t];
-            lv[t] = in ? (neg ? -xv : xv) : ty.pad;
-            const bool vt = xr[t] < IO(0);
-            negm |= ((in && neg) ? one : 0u) << t;
-            tmask |= ((in && (neg != vt)) ? one : 0u) << t;
-        }
+        for (int t = 0; t < SEG; ++t) lv[t] = (CT)xl[t];
+        // a slot's address: this pointer and a uniform row offset
+        IO *const slot = a.slot + ((size_t)i0 * a.B + b);
         // opaque: otherwise the stores re-derive the sign bits from the
         // loaded literals, which then stay live across the frequency loop
         asm volatile("" : "+v"(negm));
@@ -803,7 +857,7 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                             const IO zero = (IO)(wc * CT(0));
 #pragma unroll
                             for (int t = 0; t < SEG; ++t)
-                                if (t < nv) a.slot[(size_t)(d.off + i0 + t) * a.B + b] = zero;
+                                if (t < nv) slot[(size_t)(d.off + t) * a.B] = zero;
                         }
                     }
                     continue;
@@ -906,28 +960,19 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
                 // second gather took as long as the first: a wave reads 16 or
                 // 32 bytes of each line, and its lines do not stay in the
                 // caches); FP64 ones are read from memory again (their LDS
-                // would halve the waves per CU).  The opaque index keeps the
-                // compiler from reusing the first loads.
+                // would halve the waves per CU).
                 IO lio[SEG];
                 if constexpr (sizeof(IO) == 4) {
 #pragma unroll
                     for (int t = 0; t < SEG; ++t) lio[t] = keep[t * 64 + lane];
                 } else {
-                    int ib = i0;
-                    asm volatile("" : "+v"(ib));
-                    int lr[SEG];
-#pragma unroll
-                    for (int t = 0; t < SEG; ++t) lr[t] = lits[d.off + min(ib + t, k - 1)];
-#pragma unroll
-                    for (int t = 0; t < SEG; ++t) {
-                        const IO xv = xin[(size_t)(lr[t] & 0x7fffffff) * a.B + bb];
-                        lio[t] = t < nv ? (lr[t] < 0 ? -xv : xv) : (IO)ty.pad;
-                    }
+                    uint32_t ng, tm;
+                    load_segment<L, SEG, IO>(a, d, xin, lits, i0, bb, (IO)ty.pad, lio, nv, ng, tm);
                 }
                 seg_grad_from_moments<SEG>(lio, H, [&](int t, double g) {
                     if (t < nv) {
                         const CT gv = ((negm >> t) & 1u) ? -g : g;
-                        a.slot[(size_t)(d.off + i0 + t) * a.B + b] = (IO)(wc * gv);
+                        slot[(size_t)(d.off + t) * a.B] = (IO)(wc * gv);
                     }
                 });
             }
@@ -1007,10 +1052,9 @@ __device__ __forceinline__ void eval_unit(const EvalArgs<IO> &a, const Span sp, 
             asm volatile("" : "+v"(nv));
 #pragma unroll
             for (int t = 0; t < SEG; ++t) {
-                const int i = i0 + t;
                 if (t < nv) {
                     const CT gv = ((negm >> t) & 1u) ? -gr[t] : gr[t];
-                    a.slot[(size_t)(d.off + i) * a.B + b] = (IO)(wc * gv);
+                    slot[(size_t)(d.off + t) * a.B] = (IO)(wc * gv);
                 }
             }
         }

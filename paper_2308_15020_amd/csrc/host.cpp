@@ -982,7 +982,7 @@ static ffsat_status build_layout(ffsat_problem *p, const ffsat_problem_desc *d, 
 
     // 3. binned descriptors and literals, original -> binned positions
     std::vector<ConDesc> con((size_t)m);
-    std::vector<int32_t> lit((size_t)p->nnz);
+    std::vector<int32_t> lit((size_t)p->nnz + LIT_PAD, 0);
     std::vector<int32_t> pos((size_t)m);
     Ly.h_rk.assign((size_t)m, -1);
     int64_t off = 0;
@@ -1291,6 +1291,7 @@ static EvalArgs<IO> base_args(ffsat_plan *pl, int io, const IO *x, IO *con_val, 
     a.wm = (p->m + 31) / 32;
     a.want_grad = want_grad ? 1 : 0;
     a.want_check = 0;
+    a.x32 = points_x32(p->n, pl->B, sizeof(IO));
     a.fg = 1;
     return a;
 }

@@ -87,6 +87,14 @@ using TypeF64 = TypeT<double>;
 using FreqF32 = FreqT<float>;
 using FreqF64 = FreqT<double>;
 
+// Entries of padding past the literals: a lane reads whole segments.
+constexpr int LIT_PAD = 512;
+// EvalArgs::x32
+inline int points_x32(int n, int B, size_t es)
+{
+    return n < (1 << 24) && (int64_t)B * (int64_t)es < (1 << 24) && (int64_t)n * B * (int64_t)es <= 0xffffffffll;
+}
+
 struct ConDesc {
     int32_t off;   // first literal slot (binned literal order)
     int32_t k;     // length
@@ -218,6 +226,7 @@ struct EvalArgs {
     const void *freqs;
     int B, first, count, cpw, n_rb, fpart_row0;
     int want_grad, want_check, wm;
+    int x32;               // the points' byte offsets fit 32 bits, variables and row bytes 24
     int fg;                // root-of-unity bins: waves sharing one unit's frequencies (1, 2 or 4)
     const int32_t *skip;   // if set and *skip == 0, every wave returns at once (nothing to evaluate)
 };

@@ -84,6 +84,7 @@ extern "C" ffsat_status ffsat_eval_noalloc(const ffsat_problem *p, int32_t B, co
     a.B = B;
     a.wm = (p->m + 31) / 32;
     a.want_grad = grad ? 1 : 0;
+    a.x32 = points_x32(p->n, B, sizeof(float));
     int row0 = 0;
     for (const Bin &b : Ly.bins) {
         a.first = b.first;

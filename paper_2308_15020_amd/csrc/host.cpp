@@ -2680,10 +2680,9 @@ static hipError_t enqueue_steps(ffsat_plan *pl, float *x, int T, float *F_last, 
     return hipSuccess;
 }
 
-// The persistent loop of a small all-pulled problem (plan option): step size
-// and weight-update rate from the plan's device scalars.
-static hipError_t enqueue_iters_small(ffsat_plan *pl, float *x, int T, float *F, int32_t *n_sat, int32_t *U, bool erwa,
-                                      hipStream_t s)
+// The persistent loop of a small all-pulled problem (plan option).
+static hipError_t enqueue_iters_small(ffsat_plan *pl, float *x, int T, float *F, int32_t *n_sat, int32_t *U, float eta,
+                                      float alpha, hipStream_t s)
 {
     const PullLayout &P = pl->p->lay[IO_F32].pull[pl->persistent_class];
     PullArgs a{};
@@ -2691,11 +2690,11 @@ static hipError_t enqueue_iters_small(ffsat_plan *pl, float *x, int T, float *F,
     a.pptr = P.d_pptr;
     a.pent = P.d_pent;
     a.rk = P.d_rk;
-    a.eta_dev = pl->d_hyper;
+    a.eta = eta;
     a.n = pl->p->n;
     a.B = pl->B;
-    return launch_iters_small(PULL_E[pl->persistent_class], a, pl->p->m, P.n_ent, T, F, n_sat, U, pl->p->d_w, erwa,
-                              pl->d_hyper + 1, s);
+    return launch_iters_small(PULL_E[pl->persistent_class], a, pl->p->m, P.n_ent, T, F, n_sat, U, pl->p->d_w, alpha > 0.f,
+                              alpha, s);
 }
 
 extern "C" ffsat_status ffsat_run_steps(ffsat_plan *pl, float *x, int32_t T, float eta, float *F_last, void *stream)
@@ -2707,13 +2706,13 @@ extern "C" ffsat_status ffsat_run_steps(ffsat_plan *pl, float *x, int32_t T, flo
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
-    // the step size goes to device memory ahead of the (captured) steps
-    HIPCHK(launch_set_f32x2(pl->d_hyper, eta, 0.f, s));
     if (pl->persistent_class) {
         // one launch: all T steps in one workgroup
-        HIPCHK(enqueue_iters_small(pl, x, T, F_last, nullptr, nullptr, false, s));
+        HIPCHK(enqueue_iters_small(pl, x, T, F_last, nullptr, nullptr, eta, 0.f, s));
         return FFSAT_OK;
     }
+    // the step size goes to device memory ahead of the (captured) steps
+    HIPCHK(launch_set_f32x2(pl->d_hyper, eta, 0.f, s));
     if (!pl->use_graphs) {
         HIPCHK(enqueue_steps(pl, x, T, F_last, s));
         return FFSAT_OK;
@@ -2815,13 +2814,13 @@ extern "C" ffsat_status ffsat_run_iters(ffsat_plan *pl, float *x, int32_t T, flo
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
     const bool erwa = alpha > 0.f;
-    // step size and rate go to device memory ahead of the (captured) iterations
-    HIPCHK(launch_set_f32x2(pl->d_hyper, eta, alpha, s));
     if (pl->persistent_class) {
         // one launch: all T iterations in one workgroup
-        HIPCHK(enqueue_iters_small(pl, x, T, F, n_sat, U, erwa, s));
+        HIPCHK(enqueue_iters_small(pl, x, T, F, n_sat, U, eta, alpha, s));
         return FFSAT_OK;
     }
+    // step size and rate go to device memory ahead of the (captured) iterations
+    HIPCHK(launch_set_f32x2(pl->d_hyper, eta, alpha, s));
     auto body = [&](hipStream_t cs) {
         if (pl->iter_side) return enqueue_iters_overlapped(pl, x, T, erwa, F, n_sat, U, cs);
         return enqueue_iters(pl, x, T, erwa, F, n_sat, U, cs);

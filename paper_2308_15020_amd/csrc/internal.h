@@ -433,7 +433,7 @@ hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s);
 constexpr int ITERS_SMALL_LDS = 65536 - 512;   // leaves room for the kernel's own small arrays
 size_t iters_small_lds(int E, int n, int B, int m, int64_t n_ent);
 hipError_t launch_iters_small(int E, const PullArgs &a, int m, int64_t n_ent, int T, float *F, int32_t *n_sat,
-                              int32_t *U, float *w, bool erwa, const float *alpha_dev, hipStream_t s);
+                              int32_t *U, float *w, bool erwa, float alpha, hipStream_t s);
 
 // Maximum over a block of up to 1024 threads (values >= 0); every thread
 // gets it.  Uses red[16] and one barrier.

@@ -262,9 +262,10 @@ hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s)
 // in LDS and runs all T iterations in one launch.  Per iteration:
 //  1. one thread per (entry, restart) pair forms the entry's gradient term
 //     (the weighted leave-one-out product of its constraint) and, at the
-//     entries of first literals, the constraint's value and the exact check
-//     (U and the restart's violation count by LDS integer atomics, which
-//     are order-free);
+//     entries of first literals, where they are used (the last iteration's
+//     outputs, every weight update), the constraint's value and the exact
+//     check (U and the restart's violation count by LDS integer atomics,
+//     which are order-free);
 //  2. one thread per (variable, restart) pair adds its entries' terms in
 //     list order in FP64, rounds to FP32 as the evaluation does, and takes
 //     the projected step in place;
@@ -272,10 +273,27 @@ hipError_t launch_pull(int E, const PullArgs &a, hipStream_t s)
 // The last iteration's F is summed per variable over its first-literal
 // entries in list order (FP32), then over the variables in order (FP64):
 // every result equals that of a thread walking each pair's list alone.
+//
+// Bound by LDS latency: two barriers an iteration (three with erwa), and between
+// them a chain of dependent LDS reads on a few waves.  A thread's first pair of
+// each phase is decoded into registers once (all there is up to 1024 pairs), and
+// a variable's terms are read SUM_BATCH at a time: one read of the points and one
+// per batch are left on the chain.  50 iterations, decoding and dividing per pair and
+// iteration with terms read four at a time -> now, us: random 3-SAT n = 50, m = 213,
+// one restart 79 -> 40 (with adaptive weights 123 -> 82), 12 restarts 256 -> 176;
+// n = 100, m = 426, 4 restarts 201 -> 128; OR of 2..7, n = 60, m = 150 104 -> 53.
+constexpr int SUM_BATCH = 8;
+template <int E>
+struct SmallPair {
+    int orig, xv, xo[E - 2], km1;       // constraint; LDS index of the own point and of the others'
+    unsigned neg;                       // bit t: literal t negated, bit 31: the own one
+    float al, be, c1, c0, cst;
+    int first, chk;                     // first literal of the constraint; check threshold
+};
 template <int E>
 __global__ __launch_bounds__(1024) void k_iters_small(PullArgs a, int m, int T, float *F, int32_t *n_sat,
                                                       int32_t *Uout, float *wg, int erwa,
-                                                      const float *__restrict__ alpha_dev,
+                                                      const float alpha,
                                                       const float *__restrict__ rkt_g,
                                                       const int32_t *__restrict__ pent_g,
                                                       const int32_t *__restrict__ pptr_g)
@@ -300,117 +318,184 @@ __global__ __launch_bounds__(1024) void k_iters_small(PullArgs a, int m, int T, 
     int32_t *pent = own + n_ent;                              // [n_ent][E] entries
     float *xg = const_cast<float *>(a.x);
     const bool check = n_sat != nullptr || Uout != nullptr || erwa;
-    for (int i = threadIdx.x; i < nB; i += blockDim.x) xs[i] = xg[i];
-    for (int c = threadIdx.x; c < m; c += blockDim.x) {
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    for (int i = tid; i < nB; i += nt) xs[i] = xg[i];
+    for (int c = tid; c < m; c += nt) {
         ws[c] = wg[c];
         us[c] = 0;
     }
-    for (int b = threadIdx.x; b < B; b += blockDim.x) nu[b] = 0;
-    for (int i = threadIdx.x; i <= a.n; i += blockDim.x) pptr[i] = pptr_g[i];
-    for (int i = threadIdx.x; i < n_ent * E; i += blockDim.x) pent[i] = pent_g[i];
-    for (int i = threadIdx.x; i < RK_TABLE; i += blockDim.x) rkt[i] = rkt_g[i];
-    for (int v = threadIdx.x; v < a.n; v += blockDim.x)
+    for (int b = tid; b < B; b += nt) nu[b] = 0;
+    for (int i = tid; i <= a.n; i += nt) pptr[i] = pptr_g[i];
+    for (int i = tid; i < n_ent * E; i += nt) pent[i] = pent_g[i];
+    for (int i = tid; i < RK_TABLE; i += nt) rkt[i] = rkt_g[i];
+    for (int v = tid; v < a.n; v += nt)
         for (int p = pptr_g[v]; p < pptr_g[v + 1]; ++p) own[p] = v;
     __syncthreads();
-    const float eta = a.eta_dev != nullptr ? *a.eta_dev : a.eta;
-    const float alpha = alpha_dev != nullptr ? *alpha_dev : 0.f;
+    const float eta = a.eta;
+    // row and restart of pair tid, and what the next pair (tid + nt) adds to them
+    const int q0 = tid / B, r0 = tid - q0 * B, qs = nt / B, rs = nt - qs * B;
+    const auto decode = [&](int p, int b) {
+        SmallPair<E> s;
+        const int32_t *en = pent + (size_t)p * E;
+        const int meta = en[1], rk = meta & 7;
+        s.orig = en[0];
+        s.km1 = (meta >> 3) & 7;
+        s.chk = ((meta >> 6) & 15) - 2;
+        s.first = (meta >> 11) & 1;
+        s.neg = ((unsigned)(meta >> 10) & 1u) << 31;
+        s.xv = own[p] * B + b;
+#pragma unroll
+        for (int t = 0; t < NO; ++t) {
+            // past the constraint's length the own point, unused
+            const int o = t < s.km1 ? en[2 + t] : own[p];
+            s.neg |= ((unsigned)o >> 31) << t;
+            s.xo[t] = (o & 0x7fffffff) * B + b;
+        }
+        s.al = rkt[rk];
+        s.be = rkt[8 + rk];
+        s.c0 = rkt[16 + rk];
+        s.c1 = rkt[24 + rk];
+        s.cst = rkt[32 + rk];
+        return s;
+    };
+    const auto pair_term = [&](const SmallPair<E> &s, int i, int b, bool last) {
+        const float w = ws[s.orig];
+        float xo[NO];
+#pragma unroll
+        for (int t = 0; t < NO; ++t) xo[t] = xs[s.xo[t]];
+        const float xv = xs[s.xv];
+        float prod = 1.f;
+#pragma unroll
+        for (int t = 0; t < NO; ++t) {
+            const float f = prod * __builtin_fmaf(s.be, (s.neg >> t) & 1u ? -xo[t] : xo[t], s.al);
+            prod = t < s.km1 ? f : prod;
+        }
+        const float gterm = w * (s.c1 * prod);
+        const bool own_neg = (s.neg >> 31) != 0;
+        tg[i] = own_neg ? -gterm : gterm;
+        if ((last || erwa) && s.first) {
+            if (last) {
+                const float lown = own_neg ? -xv : xv;
+                fe[(size_t)s.orig * B + b] = __builtin_fmaf(s.c0, prod * __builtin_fmaf(s.be, lown, s.al), s.cst);
+            }
+            if (check) {
+                int cnt = (own_neg != (xv < 0.f)) ? 1 : 0;
+#pragma unroll
+                for (int t = 0; t < NO; ++t)
+                    if (t < s.km1) cnt += (((s.neg >> t) & 1u) != (xo[t] < 0.f ? 1u : 0u)) ? 1 : 0;
+                const bool sat = s.chk >= 0 ? (cnt >= s.chk) : ((cnt & 1) == (s.chk == -2 ? 1 : 0));
+                if (!sat) {
+                    atomicAdd(&us[s.orig], 1);
+                    if (last) atomicAdd(&nu[b], 1);
+                }
+            }
+        }
+    };
+    const auto sum_step = [&](int i, int b, int p0, int p1, bool last) {
+        const float xi = xs[i];
+        double acc = 0.0;
+        // the list's last, incomplete batch is read first (past the end the last
+        // term again, added as +0), then each batch at once
+        const float *tp = tg + p0 * B + b;
+        const int full = (p1 - p0) & ~(SUM_BATCH - 1), rest = p1 - p0 - full;
+        float tr[SUM_BATCH];
+        if (rest > 0) {
+            const float *te = tp + full * B;
+            const int end = (rest - 1) * B;
+#pragma unroll
+            for (int q = 0; q < SUM_BATCH; ++q) tr[q] = te[min(q * B, end)];
+        }
+        for (int p = 0; p < full; p += SUM_BATCH, tp += SUM_BATCH * B) {
+            float t[SUM_BATCH];
+#pragma unroll
+            for (int q = 0; q < SUM_BATCH; ++q) t[q] = tp[q * B];
+#pragma unroll
+            for (int q = 0; q < SUM_BATCH; ++q) acc += (double)t[q];
+        }
+        if (rest > 0) {
+#pragma unroll
+            for (int q = 0; q < SUM_BATCH - 1; ++q) acc += (double)(q < rest ? tr[q] : 0.f);
+        }
+        if (last) {
+            float facc = 0.f;
+            for (int p = p0; p < p1; p += 4) {
+                int first[4], orig[4];
+                float w[4], f[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int32_t *en = pent + (size_t)min(p + q, p1 - 1) * E;
+                    orig[q] = en[0];
+                    first[q] = p + q < p1 ? (en[1] >> 11) & 1 : 0;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    w[q] = ws[orig[q]];
+                    f[q] = fe[(size_t)orig[q] * B + b];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (first[q]) facc = __builtin_fmaf(w[q], f[q], facc);
+            }
+            fv[i] = facc;
+        }
+        const float g = (float)acc;   // same rounding as the evaluation's gradient
+        const float y = __builtin_fmaf(-eta, g, xi);
+        xs[i] = fminf(fmaxf(y, -1.0f), 1.0f);
+    };
+    SmallPair<E> mine = decode(min(q0, n_ent - 1), r0);
+    const int pa = pptr[min(q0, a.n - 1)], pb = pptr[min(q0, a.n - 1) + 1];
 #pragma unroll 1
     for (int it = 0; it < T; ++it) {
+        const bool last = it == T - 1;
         // 1. entry terms at x_t
-        for (int i = threadIdx.x; i < eB; i += blockDim.x) {
-            const int p = i / B, b = i - p * B;
-            const int32_t *en = pent + (size_t)p * E;
-            const int orig = en[0], meta = en[1];
-            const int rk = meta & 7, km1 = (meta >> 3) & 7;
-            const bool own_neg = (meta >> 10) & 1;
-            const float al = rkt[rk], be = rkt[8 + rk];
-            float prod = 1.f;
-            int cnt = 0;
-#pragma unroll
-            for (int t = 0; t < NO; ++t) {
-                if (t < km1) {
-                    const int o = en[2 + t];
-                    const float xo = xs[(o & 0x7fffffff) * B + b];
-                    prod *= __builtin_fmaf(be, o < 0 ? -xo : xo, al);
-                    cnt += ((o < 0) != (xo < 0.f)) ? 1 : 0;
-                }
+        if (tid < eB) pair_term(mine, tid, r0, last);
+        for (int i = tid + nt, p = q0 + qs, b = r0 + rs; i < eB; i += nt, p += qs, b += rs) {
+            if (b >= B) {
+                b -= B;
+                ++p;
             }
-            const float gterm = ws[orig] * (rkt[24 + rk] * prod);
-            tg[i] = own_neg ? -gterm : gterm;
-            if ((meta >> 11) & 1) {
-                const float xv = xs[own[p] * B + b];
-                const float lown = own_neg ? -xv : xv;
-                fe[(size_t)orig * B + b] = __builtin_fmaf(rkt[16 + rk], prod * __builtin_fmaf(be, lown, al), rkt[32 + rk]);
-                if (check) {
-                    cnt += (own_neg != (xv < 0.f)) ? 1 : 0;
-                    const int chk = ((meta >> 6) & 15) - 2;
-                    const bool sat = chk >= 0 ? (cnt >= chk) : ((cnt & 1) == (chk == -2 ? 1 : 0));
-                    if (!sat) {
-                        atomicAdd(&us[orig], 1);
-                        atomicAdd(&nu[b], 1);
-                    }
-                }
-            }
+            pair_term(decode(p, b), i, b, last);
         }
         __syncthreads();
         // 2. ordered sums and the step; the last iteration's objective sums
-        const bool last = it == T - 1;
-        for (int i = threadIdx.x; i < nB; i += blockDim.x) {
-            const int v = i / B, b = i - v * B;
-            const int p0 = pptr[v], p1 = pptr[v + 1];
-            double acc = 0.0;
-            int p = p0;
-            for (; p + 4 <= p1; p += 4) {
-                const float t0 = tg[(p + 0) * B + b], t1 = tg[(p + 1) * B + b];
-                const float t2 = tg[(p + 2) * B + b], t3 = tg[(p + 3) * B + b];
-                acc += (double)t0;
-                acc += (double)t1;
-                acc += (double)t2;
-                acc += (double)t3;
+        if (tid < nB) sum_step(tid, r0, pa, pb, last);
+        for (int i = tid + nt, v = q0 + qs, b = r0 + rs; i < nB; i += nt, v += qs, b += rs) {
+            if (b >= B) {
+                b -= B;
+                ++v;
             }
-            for (; p < p1; ++p) acc += (double)tg[p * B + b];
-            if (last) {
-                float facc = 0.f;
-                for (int q = p0; q < p1; ++q) {
-                    const int32_t *en = pent + (size_t)q * E;
-                    if ((en[1] >> 11) & 1) facc = __builtin_fmaf(ws[en[0]], fe[(size_t)en[0] * B + b], facc);
-                }
-                fv[i] = facc;
-            }
-            const float g = (float)acc;   // same rounding as the evaluation's gradient
-            const float y = __builtin_fmaf(-eta, g, xs[i]);
-            xs[i] = fminf(fmaxf(y, -1.0f), 1.0f);
+            sum_step(i, b, pptr[v], pptr[v + 1], last);
         }
         if (last) {
             __syncthreads();
-            for (int b = threadIdx.x; b < B; b += blockDim.x) {
+            for (int b = tid; b < B; b += nt) {
                 double f = 0.0;
+#pragma unroll 16
                 for (int v = 0; v < a.n; ++v) f += (double)fv[v * B + b];
                 if (F != nullptr) F[b] = (float)f;
                 if (n_sat != nullptr) n_sat[b] = m - nu[b];
             }
             if (Uout != nullptr)
-                for (int c = threadIdx.x; c < m; c += blockDim.x) Uout[c] = us[c];
+                for (int c = tid; c < m; c += nt) Uout[c] = us[c];
         }
         // 3. weights (the counts are complete since the barrier after 1.;
-        // the weights were last read in 2.)
+        // the weights were last read in 2.: block_max_1024 has a barrier); each
+        // thread clears the counts that it alone reads here
         if (erwa) {
             int32_t mx = 0;
-            for (int c = threadIdx.x; c < m; c += blockDim.x) mx = max(mx, us[c]);
+            for (int c = tid; c < m; c += nt) mx = max(mx, us[c]);
             const int32_t umax = block_max_1024(mx, red);
             const float inv = umax > 0 ? 1.0f / (float)umax : 0.0f;
-            for (int c = threadIdx.x; c < m; c += blockDim.x) ws[c] = erwa_weight(ws[c], us[c], umax, inv, alpha);
+            for (int c = tid; c < m; c += nt) {
+                ws[c] = erwa_weight(ws[c], us[c], umax, inv, alpha);
+                us[c] = 0;
+            }
         }
-        __syncthreads();   // every count read before it is cleared; the step and weights before the next terms
-        if (check) {
-            for (int c = threadIdx.x; c < m; c += blockDim.x) us[c] = 0;
-            for (int b = threadIdx.x; b < B; b += blockDim.x) nu[b] = 0;
-        }
-        __syncthreads();
+        __syncthreads();   // the step and weights before the next terms
     }
-    for (int i = threadIdx.x; i < nB; i += blockDim.x) xg[i] = xs[i];
+    for (int i = tid; i < nB; i += nt) xg[i] = xs[i];
     if (erwa)
-        for (int c = threadIdx.x; c < m; c += blockDim.x) wg[c] = ws[c];
+        for (int c = tid; c < m; c += nt) wg[c] = ws[c];
 }
 
 size_t iters_small_lds(int E, int n, int B, int m, int64_t n_ent)
@@ -420,7 +505,7 @@ size_t iters_small_lds(int E, int n, int B, int m, int64_t n_ent)
 }
 
 hipError_t launch_iters_small(int E, const PullArgs &a, int m, int64_t n_ent, int T, float *F, int32_t *n_sat,
-                              int32_t *U, float *w, bool erwa, const float *alpha_dev, hipStream_t s)
+                              int32_t *U, float *w, bool erwa, float alpha, hipStream_t s)
 {
     if (T <= 0) return hipSuccess;
     const int64_t work = std::max<int64_t>(std::max<int64_t>(n_ent * a.B, (int64_t)a.n * a.B), m);
@@ -429,10 +514,10 @@ hipError_t launch_iters_small(int E, const PullArgs &a, int m, int64_t n_ent, in
     const int threads = work >= 1024 ? 1024 : (int)((work + 63) / 64) * 64;
     if (E == 4)
         hipLaunchKernelGGL((k_iters_small<4>), dim3(1), dim3(threads), lds, s, a, m, T, F, n_sat, U, w, erwa ? 1 : 0,
-                           alpha_dev, a.rk, a.pent, a.pptr);
+                           alpha, a.rk, a.pent, a.pptr);
     else if (E == 8)
         hipLaunchKernelGGL((k_iters_small<8>), dim3(1), dim3(threads), lds, s, a, m, T, F, n_sat, U, w, erwa ? 1 : 0,
-                           alpha_dev, a.rk, a.pent, a.pptr);
+                           alpha, a.rk, a.pent, a.pptr);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

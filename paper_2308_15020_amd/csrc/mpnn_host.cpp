@@ -117,7 +117,10 @@ ffsat_status ensure_ws(ffsat_mpnn *net, int n, int m)
         (st = get(N * H, &net->dHv)) || (st = get(Mc * H, &net->dHc)) || (st = get(N * 3 * H, &net->dXv)) ||
         (st = get(Mc * 3 * H, &net->dXc)))
         return st;
-    net->part_len = (size_t)64 * (3 * H + 1) * H;
+    // partials of every weight gradient at its most slices, at most 64 MB (then
+    // summed more than once a pass) unless one launch's take more
+    const size_t layer = (size_t)64 * (3 * H + 1) * H, input = (size_t)2 * 64 * 9 * H;
+    net->part_len = std::max(layer, std::min((size_t)2 * net->R * layer + input, (size_t)1 << 24));
     if ((st = get(net->part_len, &net->part)) || (st = get((size_t)HEAD_SLICES * (H + 2), &net->cpart))) return st;
     net->cap_n = n;
     net->cap_m = m;
@@ -221,39 +224,53 @@ ffsat_status graph_of(ffsat_problem *p, MpnnGraph **out)
 // of loads per wave) up to 64 slices, the size of the partials' buffer.
 int splits_for(int K) { return std::max(1, std::min(64, (K + 127) / 128)); }
 
-// dW (K x H) = X^T dZ over `rows` rows and the bias gradient (column sums of
-// dZ, which follow dW in the parameter order), split over the rows,
-// fixed-order sum
-hipError_t weight_grad(ffsat_mpnn *net, int rows, int K, const float *X, int ldx, const float *dZ, float *out,
-                       hipStream_t s)
-{
-    const int H = net->H;
-    int S = splits_for(rows);
-    const size_t len = (size_t)(K + 1) * H;
-    while ((size_t)S * len > net->part_len && S > 1) S /= 2;
-    hipError_t e = gemm(true, false, 0, K, H, rows, X, ldx, dZ, H, net->part, H, nullptr, S, len, s, true);
-    if (e != hipSuccess) return e;
-    // exactly the slices the product wrote
-    return sum_slices((int64_t)len, gemm_slices(rows, S), net->part, len, out, s);
-}
+size_t weight_part(int rows, int K, int H) { return (size_t)gemm_slices(rows, splits_for(rows)) * (size_t)(K + 1) * H; }
+
+// The weight gradients of a backward pass: their partials follow one another in
+// the plan's buffer and are summed in one launch at the end (or before the
+// buffer is full).
+struct WeightSums {
+    ffsat_mpnn *net;
+    SumJobs jobs;
+    size_t used = 0;
+    // room for the partials of the next launch
+    hipError_t reserve(size_t len, hipStream_t s)
+    {
+        if (used + len <= net->part_len) return hipSuccess;
+        used = 0;
+        return sum_slices(jobs, s);
+    }
+    // dW (K x H) = X^T dZ over `rows` rows and the bias gradient (column sums of
+    // dZ, which follow dW in the parameter order), split over the rows,
+    // fixed-order sum
+    GemmArgs grad(int rows, int K, const float *X, int ldx, const float *dZ, float *out)
+    {
+        const int H = net->H, S = splits_for(rows);
+        const size_t len = (size_t)(K + 1) * H;
+        float *part = net->part + used;
+        used += weight_part(rows, K, H);
+        jobs.job[jobs.n++] = SumJob{part, len, (int)len, 0, gemm_slices(rows, S), 0, out, nullptr};
+        return gemm_args(true, false, 0, K, H, rows, X, ldx, dZ, H, part, H, nullptr, S, len);
+    }
+};
 
 ffsat_status forward(ffsat_mpnn *net, MpnnGraph *g, hipStream_t s)
 {
     const int H = net->H, n = g->n, m = g->m;
     const float *W = net->w;
     const auto &o = net->off;
-    MCHK(gemm(false, false, 1, n, H, 8, g->fv, 8, W + o[P_EV], H, net->hv0, H, W + o[P_EVB], 1, 0, s));
-    MCHK(gemm(false, false, 1, m, H, 8, g->fc, 8, W + o[P_EC], H, net->hc0, H, W + o[P_ECB], 1, 0, s));
+    MCHK(gemm_relu2(gemm_args(false, false, 1, n, H, 8, g->fv, 8, W + o[P_EV], H, net->hv0, H, W + o[P_EVB], 1, 0),
+                    gemm_args(false, false, 1, m, H, 8, g->fc, 8, W + o[P_EC], H, net->hc0, H, W + o[P_ECB], 1, 0), s));
     const float *hv = net->hv0, *hc = net->hc0;
     for (int r = 0; r < net->R; ++r) {
         // messages into columns H..3H of X, the constraint's own state into 0..H
         MCHK(gather(0, m, H, g->con_ptr, g->var_of, g->lit, g->wk, hv, H, net->Xc[r], 3 * H, hc, H, nullptr, s));
-        MCHK(gemm(false, false, 1, m, H, 3 * H, net->Xc[r], 3 * H, W + o[p_wc(r)], H, net->Hc[r], H, W + o[p_bc(r)], 1,
-                  0, s));
+        MCHK(gemm_relu(gemm_args(false, false, 1, m, H, 3 * H, net->Xc[r], 3 * H, W + o[p_wc(r)], H, net->Hc[r], H,
+                                 W + o[p_bc(r)], 1, 0), s));
         hc = net->Hc[r];
         MCHK(gather(0, n, H, g->vptr, g->vcon, g->vlit, g->vwd, hc, H, net->Xv[r], 3 * H, hv, H, nullptr, s));
-        MCHK(gemm(false, false, 1, n, H, 3 * H, net->Xv[r], 3 * H, W + o[p_wv(r)], H, net->Hv[r], H, W + o[p_bv(r)], 1,
-                  0, s));
+        MCHK(gemm_relu(gemm_args(false, false, 1, n, H, 3 * H, net->Xv[r], 3 * H, W + o[p_wv(r)], H, net->Hv[r], H,
+                                 W + o[p_bv(r)], 1, 0), s));
         hv = net->Hv[r];
     }
     MCHK(head(n, H, hv, W + o[p_wo(net->R)], W + o[p_wo(net->R) + 1], net->mu, s));
@@ -269,21 +286,28 @@ ffsat_status backward(ffsat_mpnn *net, MpnnGraph *g, const float *target, float 
     // dHv, dHc hold each layer's gradient already taken back through its ReLU:
     // the kernels that produce it read the layer's output and the own columns
     // of the product above in place
+    WeightSums sums{net};
     MCHK(head_back(n, H, net->mu, target, W + o[p_wo(R)], net->Hv[R - 1], net->dz, net->lterm, net->dHv, s));
-    MCHK(head_sums(n, H, net->dz, net->lterm, net->Hv[R - 1], net->cpart, G + o[p_wo(R)], loss, s));   // wo then bo
+    MCHK(head_sums(n, H, net->dz, net->lterm, net->Hv[R - 1], net->cpart, G + o[p_wo(R)], loss, sums.jobs, s));   // wo then bo
     for (int r = R - 1; r >= 0; --r) {
-        MCHK(weight_grad(net, n, 3 * H, net->Xv[r], 3 * H, net->dHv, G + o[p_wv(r)], s));
-        MCHK(gemm(false, true, 0, n, 3 * H, H, net->dHv, H, W + o[p_wv(r)], H, net->dXv, 3 * H, nullptr, 1, 0, s));
+        MCHK(sums.reserve(weight_part(n, 3 * H, H), s));
+        MCHK(gemm_back(sums.grad(n, 3 * H, net->Xv[r], 3 * H, net->dHv, G + o[p_wv(r)]),
+                       gemm_args(false, true, 0, n, 3 * H, H, net->dHv, H, W + o[p_wv(r)], H, net->dXv, 3 * H, nullptr, 1,
+                                 0), s));
         MCHK(gather(1, m, H, g->con_ptr, g->var_of, g->lit, g->wd, net->dXv, 3 * H, net->dHc, H,
                     r == R - 1 ? nullptr : net->dXc, 3 * H, net->Hc[r], s));
-        MCHK(weight_grad(net, m, 3 * H, net->Xc[r], 3 * H, net->dHc, G + o[p_wc(r)], s));
-        MCHK(gemm(false, true, 0, m, 3 * H, H, net->dHc, H, W + o[p_wc(r)], H, net->dXc, 3 * H, nullptr, 1, 0, s));
+        MCHK(sums.reserve(weight_part(m, 3 * H, H), s));
+        MCHK(gemm_back(sums.grad(m, 3 * H, net->Xc[r], 3 * H, net->dHc, G + o[p_wc(r)]),
+                       gemm_args(false, true, 0, m, 3 * H, H, net->dHc, H, W + o[p_wc(r)], H, net->dXc, 3 * H, nullptr, 1,
+                                 0), s));
         MCHK(gather(1, n, H, g->vptr, g->vcon, g->vlit, g->vwk, net->dXc, 3 * H, net->dHv, H, net->dXv, 3 * H,
                     r > 0 ? net->Hv[r - 1] : net->hv0, s));
     }
-    MCHK(weight_grad(net, n, 8, g->fv, 8, net->dHv, G + o[P_EV], s));
     MCHK(relu_back(m, H, net->dHc, net->hc0, net->dXc, 3 * H, s));
-    MCHK(weight_grad(net, m, 8, g->fc, 8, net->dHc, G + o[P_EC], s));
+    MCHK(sums.reserve(weight_part(n, 8, H) + weight_part(m, 8, H), s));
+    const GemmArgs ev = sums.grad(n, 8, g->fv, 8, net->dHv, G + o[P_EV]);
+    MCHK(gemm_weights2(ev, sums.grad(m, 8, g->fc, 8, net->dHc, G + o[P_EC]), s));
+    MCHK(sum_slices(sums.jobs, s));
     return FFSAT_OK;
 }
 

@@ -43,6 +43,13 @@ __global__ __launch_bounds__(RED_BLOCK) void k_reduce(ReduceArgs<IO> a, int n_gr
         const int b = (int)blockIdx.y * RED_BLOCK + ((wave % WPV) * 64 + (int)(threadIdx.x & 63)) * VEC;
         if (v >= n_grad || b >= B) return;
         using V = VecT<IO, VEC>;
+        if constexpr (!STEP) {
+            if (a.copy_src != nullptr) {
+                const size_t i = (size_t)v * B + b;
+                *reinterpret_cast<V *>(&a.copy_dst[i]) = *reinterpret_cast<const V *>(&a.copy_src[i]);
+                return;
+            }
+        }
         const int e0 = a.vptr[v], e1 = a.vptr[v + 1];
         double acc[VEC] = {};
         int e = e0;
@@ -158,14 +165,14 @@ __global__ __launch_bounds__(64 * FSUM_WAVES) void k_fsum2(ReduceArgs<IO> a, int
 template <typename IO, bool STEP>
 static hipError_t reduce_impl(const ReduceArgs<IO> &a, hipStream_t s, int parts = 3)
 {
-    const bool want_g = STEP ? (a.x_step != nullptr) : (a.grad != nullptr);
+    const bool want_g = STEP ? (a.x_step != nullptr) : (a.grad != nullptr || a.copy_src != nullptr);
     const int n_grad = want_g ? a.n : 0;
     const bool rows = a.F != nullptr || a.n_sat != nullptr;
     const int splits = rows ? f_splits(a.rows) : 0;
     if ((parts & 1) && n_grad + splits > 0) {
         const auto fits = [&](int vec) {
             const auto al = [&](const void *p) { return ((uintptr_t)p & (sizeof(IO) * (size_t)vec - 1)) == 0; };
-            return a.B % vec == 0 && al(a.slot) && al(a.grad) && al(a.x_step);
+            return a.B % vec == 0 && al(a.slot) && al(a.grad) && al(a.x_step) && al(a.copy_src) && al(a.copy_dst);
         };
         const auto go = [&](auto vec) {
             constexpr int VEC = decltype(vec)::value;

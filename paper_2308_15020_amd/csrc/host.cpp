@@ -2775,7 +2775,7 @@ static hipError_t enqueue_iters_overlapped(ffsat_plan *pl, float *x, int T, bool
     if (U) ITER_CHK(launch_fill_i32(U, p->m, 0, s));
     // an odd count: the first pull steps from a copy of x back into x.  The copy
     // runs beside the first bins, which read x (100000 variables, 256 restarts:
-    // an iteration 2180 -> 2148 us); with nothing to run beside, it takes as long at the end
+    // an iteration 2180 -> 2148 us); with nothing to run beside, it goes with the last sums
     const bool ahead = pull && T % 2 == 1 && pl->bins[IO_F32][0].pk < pull;
     if (ahead) {
         ITER_CHK(hipEventRecord(pl->ev_aux, s));
@@ -2801,7 +2801,13 @@ static hipError_t enqueue_iters_overlapped(ffsat_plan *pl, float *x, int T, bool
         if (U && t < T - 1) ITER_CHK(launch_fill_i32(U, p->m, 0, q));
         ITER_CHK(hipEventRecord(pl->ev_aux, q));
         if (t > 0) ITER_CHK(hipStreamWaitEvent(s, pl->ev_sum, 0));   // level-2 sums of t-1 read the level-1 rows
-        const ReduceArgs<float> r = reduce_args<float>(pl, IO_F32, nullptr, cur, 0.f, pl->d_hyper, nullptr, F, n_sat, pull);
+        ReduceArgs<float> r = reduce_args<float>(pl, IO_F32, nullptr, cur, 0.f, pl->d_hyper, nullptr, F, n_sat, pull);
+        if (pull && t == T - 1 && nxt != x) {
+            // the points back into x in the launch of the sums (with one of its own one
+            // iteration at n = 53, 142 clauses of 3, 239 restarts took 75 us, now 71)
+            r.copy_src = nxt;
+            r.copy_dst = x;
+        }
         ITER_CHK(launch_reduce_part_f32(r, 1, s));
         ITER_CHK(hipEventRecord(pl->ev_red, s));
         ITER_CHK(hipStreamWaitEvent(q, pl->ev_red, 0));
@@ -2810,7 +2816,6 @@ static hipError_t enqueue_iters_overlapped(ffsat_plan *pl, float *x, int T, bool
         if (pull) std::swap(cur, nxt);
     }
     ITER_CHK(hipStreamWaitEvent(s, pl->ev_sum, 0));
-    if (cur != x) ITER_CHK(launch_copy_f32(x, cur, (int64_t)p->n * pl->B, s));
 #undef ITER_CHK
     return hipSuccess;
 }

@@ -390,6 +390,8 @@ struct ReduceArgs {
     IO *F;
     int32_t *n_sat;
     const int32_t *skip;   // if set and *skip == 0, the reduction does nothing
+    const IO *copy_src;    // without grad and x_step: [n][B] values copied to copy_dst beside the sums
+    IO *copy_dst;
 };
 hipError_t launch_reduce_f32(const ReduceArgs<float> &r, hipStream_t s);
 

@@ -308,11 +308,11 @@ def measure(name, args, dev, headline):
         elif desc["pull"]:
             nbytes = 8.0 * desc["objective_rows"] * B
             ent = roofline_entry("objective and count row sums", 0.0, nbytes, "f32", avg_s, per_step)
-            ent["kernel_name"] = f"k_reduce<float, false, {4 if B % 4 == 0 else 1}>"
+            ent["kernel_name"] = f"k_reduce<float, false, {4 if B % 4 == 0 else 2 if B % 2 == 0 else 1}>"
         else:
             nbytes = (4.0 * inst.nnz + 8.0 * inst.n_vars) * B
             ent = roofline_entry("gradient reduction + projected step", 0.0, nbytes, "f32", avg_s, per_step)
-            ent["kernel_name"] = f"k_reduce<float, true, {4 if B % 4 == 0 else 1}>"
+            ent["kernel_name"] = f"k_reduce<float, true, {4 if B % 4 == 0 else 2 if B % 2 == 0 else 1}>"
         ent["ms_per_step"] = avg_s * 1e3 * per_step
         entries.append(ent)
     # kernels of one template are reported together (split bins of one shape)

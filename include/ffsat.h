@@ -127,13 +127,15 @@ typedef struct {
                                 with the others beside it; reserved[2]: gradient of
                                 the transform-free constraints of length <= 7
                                 (OR, AND, XOR, constants), 0 automatic (the
-                                autotuner decides; off without it), 1 through
+                                autotuner decides; without it 3 if reserved[1]
+                                is 0 and every constraint of the problem is one
+                                of at most 3 literals, else off), 1 through
                                 per-literal slots and the slot reduction, 2 gathered
                                 per variable for lengths <= 7, 3 for lengths <= 3
-                                (the pulled gradient; never with launch structure 2,
-                                never for n * B above 2^29); reserved[3]:
+                                (the pulled gradient; never with a fixed launch
+                                structure 2, never for n * B above 2^29); reserved[3]:
                                 variables per wave of the pulled gradient, 0..8
-                                (0 = 8); reserved[4] = 1: ffsat_run_steps and
+                                (0: 1, or 2 from n = 32768 on); reserved[4] = 1: ffsat_run_steps and
                                 ffsat_run_iters run all T iterations in one
                                 persistent launch of one workgroup (points,
                                 per-occurrence gradient terms, constraint values,
@@ -227,7 +229,7 @@ ffsat_status ffsat_eval(ffsat_plan *plan, const float *x, float *F, float *grad,
 /* ffsat_eval plus the exact check of the same point (see ffsat_round_check
  * for the outputs n_sat, unsat_bits, U), in the same kernels: each literal
  * is gathered once for both.  With F, grad and con_val all NULL only the
- * check runs. */
+ * check runs, as ffsat_round_check. */
 ffsat_status ffsat_eval_check(ffsat_plan *plan, const float *x, float *F, float *grad,
                               float *con_val, int32_t *n_sat, uint32_t *unsat_bits, int32_t *U,
                               void *stream);

@@ -24,7 +24,7 @@
 // coefficients.  Padding literals have p = 0.
 // Measured against the running products (grouped launch of every bin): mixed n =
 // 2000 instance (200 constraints of 10..100 literals among 8500 others) 196 -> 116 us
-// at 1024 restarts, 55 -> 38 at 256; 200 constraints of 32 literals at 10000 points
+// at 1024 restarts, 55 -> 34 at 256; 200 constraints of 32 literals at 10000 points
 // 284 -> 160.  In a launch of its own beside the others, without the few spills of
 // its 24- and 32-literal shapes at four waves per SIMD: slower (mixed round 483 ->
 // 627 us, one more launch per step).

@@ -17,7 +17,8 @@
 // over the L lanes (DPP row shifts for L <= 16).  FP64 root-of-unity bins
 // evaluate each segment's product as a polynomial in the frequency's factor
 // coefficient and accumulate per-degree moments for the gradient (the
-// polynomial form, below).  Constraint descriptors and
+// polynomial form, below); from NODE_MIN_LEN literals on, at-least-t takes only
+// the frequencies its points need (node_window).  Constraint descriptors and
 // coefficient tables are wave-uniform (scalar loads, the next frequency's
 // entry prefetched); literal values are gathered from x[v][b] with restarts
 // contiguous, so a wave reads 64/L consecutive restarts of a variable per

@@ -39,6 +39,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     extern __shared__ __align__(16) char group_lds[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     __shared__ double stage[4 * wave_doubles<IO>(32)];   // FP32 points 40 KB: 3 blocks of 4 waves a CU, as the registers allow
+    if (a.skip != nullptr && *a.skip == 0) return;   // before the block table: nothing else to wait for
     const int2 bw = blk[blockIdx.x];
     const GroupEntry e = ent[__builtin_amdgcn_readfirstlane(bw.x)];
     const Span sp{e.first, e.count, e.cpw, e.n_rb, e.fpart_row0};

@@ -518,15 +518,22 @@ __global__ __launch_bounds__(256) void k_fista_trial(int n, int B, int rows, int
 // Objective of the trial point and sufficient-decrease test per searching
 // restart: a block of 16 waves per 64 restarts; each wave adds a contiguous share
 // of the objective rows and of the trial's partial sums in order (FP64), wave 0
-// the waves' sums in wave order (fixed, deterministic).  On failure eta halves;
+// the waves' sums in wave order (fixed, deterministic).  The rows are added as the
+// two levels of the objective's sum add them (k_reduce, k_fsum2: splits of `per` rows
+// rounded to FP32, the waves' shares whole splits): F(z) and F(y) of one point
+// are then the same number, and a step that does not move passes the test.  Summed
+// otherwise, one in ten such restarts had F(z) an ulp above F(y), failed
+// every trial and stopped (3-SAT, n = 250, uniform weights).  On failure eta halves;
 // after the last trial the point is taken anyway.  pending counts the restarts
 // still searching after this trial.  One launch instead of the two levels of the
 // objective's sum and a test that walked the partial sums on one wave (65 us at
 // 2000 variables): a trial slot is three launches, which is all that an unneeded
 // one costs.
 static constexpr int ACCEPT_WAVES = 16;
-__global__ __launch_bounds__(64 * ACCEPT_WAVES) void k_fista_accept(int B, int frows, const float *__restrict__ fpart,
-                                                                    int chunks, const float *__restrict__ part,
+static_assert(ACCEPT_WAVES == FSUM_WAVES, "the second level's shares");
+__global__ __launch_bounds__(64 * ACCEPT_WAVES) void k_fista_accept(int B, int frows, int per,
+                                                                    const float *__restrict__ fpart, int chunks,
+                                                                    const float *__restrict__ part,
                                                                     const float *__restrict__ Fy, float *eta,
                                                                     int32_t *searching, float *Fout, int last,
                                                                     int32_t *pending, const int32_t *__restrict__ skip)
@@ -540,9 +547,15 @@ __global__ __launch_bounds__(64 * ACCEPT_WAVES) void k_fista_accept(int B, int f
     const int bb = b < B ? b : B - 1;
     double f = 0.0, dot = 0.0, sq = 0.0;
     if (on) {
-        const int r0 = (int)((int64_t)frows * w / ACCEPT_WAVES), r1 = (int)((int64_t)frows * (w + 1) / ACCEPT_WAVES);
+        const int splits = (frows + per - 1) / per;
+        const int s0 = (int)((int64_t)splits * w / ACCEPT_WAVES), s1 = (int)((int64_t)splits * (w + 1) / ACCEPT_WAVES);
+        for (int q = s0; q < s1; ++q) {
+            const int r1 = min(frows, (q + 1) * per);
+            double acc = 0.0;
 #pragma unroll 16
-        for (int r = r0; r < r1; ++r) f += (double)fpart[(size_t)r * B + bb];
+            for (int r = q * per; r < r1; ++r) acc += (double)fpart[(size_t)r * B + bb];
+            f += (double)(float)acc;
+        }
         const int c0 = (int)((int64_t)chunks * w / ACCEPT_WAVES), c1 = (int)((int64_t)chunks * (w + 1) / ACCEPT_WAVES);
 #pragma unroll 8
         for (int c = c0; c < c1; ++c) {
@@ -625,14 +638,14 @@ hipError_t launch_fista_trial(int n, int B, const float *y, const float *g, cons
     return hipGetLastError();
 }
 
-hipError_t launch_fista_accept(int n, int B, int frows, const float *fpart, const float *part, const float *Fy, float *eta,
-                               int32_t *searching, float *Fout, int last, int32_t *pending, const int32_t *skip,
-                               hipStream_t s)
+hipError_t launch_fista_accept(int n, int B, int frows, bool summed, const float *fpart, const float *part,
+                               const float *Fy, float *eta, int32_t *searching, float *Fout, int last, int32_t *pending,
+                               const int32_t *skip, hipStream_t s)
 {
     const int rows = fista_rows(n, B);
     const int chunks = (n + rows - 1) / rows;
-    hipLaunchKernelGGL(k_fista_accept, dim3((B + 63) / 64), dim3(64 * ACCEPT_WAVES), 0, s, B, frows, fpart, chunks, part, Fy,
-                       eta, searching, Fout, last, pending, skip);
+    hipLaunchKernelGGL(k_fista_accept, dim3((B + 63) / 64), dim3(64 * ACCEPT_WAVES), 0, s, B, frows,
+                       summed ? 1 : F_ROWS_PER_SPLIT, fpart, chunks, part, Fy, eta, searching, Fout, last, pending, skip);
     return hipGetLastError();
 }
 

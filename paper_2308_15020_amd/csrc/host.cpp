@@ -1793,7 +1793,7 @@ template <typename IO>
 static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *con_val, int32_t *n_sat,
                              uint32_t *unsat_bits, int32_t *U, float *x_step, float eta, hipStream_t s,
                              const float *eta_dev = nullptr, const int32_t *skip = nullptr,
-                             float *x_next = nullptr);
+                             float *x_next = nullptr, bool allow_pull = true);
 
 // Tiling of k_pull: one variable per wave (a wave's variables follow one
 // another, four dependent loads each), two from 32768 variables on, and up to
@@ -2473,11 +2473,12 @@ static ffsat_status run_check(ffsat_plan *pl, const IO *x, uint32_t *assign_bits
 // One evaluation pass: optional value/gradient/objective outputs, optional
 // exact check of the same point, optional fused projected step (in place
 // into x_step; with the pull path, into x_next when given, else through
-// the plan's second point buffer and a copy back).
+// the plan's second point buffer and a copy back).  allow_pull = false keeps to
+// the slots.
 template <typename IO>
 static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *con_val, int32_t *n_sat,
                              uint32_t *unsat_bits, int32_t *U, float *x_step, float eta, hipStream_t s,
-                             const float *eta_dev, const int32_t *skip, float *x_next)
+                             const float *eta_dev, const int32_t *skip, float *x_next, bool allow_pull)
 {
     const int io = sizeof(IO) == 4 ? IO_F32 : IO_F64;
     const ffsat_problem *p = pl->p;
@@ -2485,7 +2486,7 @@ static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *c
     if (U) HIPCHK(launch_fill_i32(U, p->m, 0, s));
     if (unsat_bits) HIPCHK(launch_fill_i32((int32_t *)unsat_bits, (int64_t)((p->m + 31) / 32) * pl->B, 0, s));
     const bool grad_slots = grad != nullptr || x_step != nullptr;
-    const int pull = pull_on(pl, io, con_val, grad_slots) ? pl->pull : 0;
+    const int pull = allow_pull && pull_on(pl, io, con_val, grad_slots) ? pl->pull : 0;
     EvalArgs<IO> a = base_args<IO>(pl, io, x, con_val, grad_slots);
     a.want_check = want_check ? 1 : 0;
     a.unsat_bits = unsat_bits;
@@ -2940,8 +2941,10 @@ static hipError_t enqueue_fista_iter(ffsat_plan *pl, float *x, float *y, float *
     hipError_t e;
     if ((e = launch_fill_i32(pending, max_ls + 1, 0, s)) != hipSuccess) return e;
     if ((e = launch_fista_begin(B, eta, active, searching, pending, s)) != hipSuccess) return e;
+    // F(y) from the bins that give F(z) and never from the pulled gradient's rows,
+    // which add in another order: the test compares the two (k_fista_accept)
     if (run_eval<float>(pl, y, pl->d_fFy, pl->d_fg, nullptr, nullptr, nullptr, nullptr, nullptr, 0.f, s, nullptr,
-                        pending) != FFSAT_OK)
+                        pending, nullptr, false) != FFSAT_OK)
         return hipErrorUnknown;
     for (int q = 0; q < max_ls; ++q) {
         if ((e = launch_fista_trial(n, B, y, pl->d_fg, eta, searching, pl->d_fz, pl->d_fpartial, pending + q, s)) !=
@@ -2953,7 +2956,8 @@ static hipError_t enqueue_fista_iter(ffsat_plan *pl, float *x, float *y, float *
         if ((e = enqueue_bins<float>(pl, IO_F32, a, s)) != hipSuccess) return e;
         int rows = eval_rows(pl, IO_F32, 0);
         const float *fpart = (const float *)pl->d_fpart[IO_F32];
-        if (rows > FISTA_ROWS) {
+        const bool summed = rows > FISTA_ROWS;
+        if (summed) {
             // F only asks for the rows' first level here
             const ReduceArgs<float> r = reduce_args<float>(pl, IO_F32, nullptr, nullptr, 0.f, nullptr, pending + q,
                                                            pl->d_fFy, nullptr, 0);
@@ -2961,7 +2965,7 @@ static hipError_t enqueue_fista_iter(ffsat_plan *pl, float *x, float *y, float *
             fpart = (const float *)pl->d_ftmp[IO_F32];
             rows = f_splits(rows);
         }
-        if ((e = launch_fista_accept(n, B, rows, fpart, pl->d_fpartial, pl->d_fFy, eta, searching, F,
+        if ((e = launch_fista_accept(n, B, rows, summed, fpart, pl->d_fpartial, pl->d_fFy, eta, searching, F,
                                      q == max_ls - 1 ? 1 : 0, pending + q + 1, pending + q, s)) != hipSuccess)
             return e;
     }

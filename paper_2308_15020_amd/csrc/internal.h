@@ -510,10 +510,11 @@ hipError_t launch_fista_begin(int B, const float *eta, int32_t *active, int32_t 
                               hipStream_t s);
 hipError_t launch_fista_trial(int n, int B, const float *y, const float *g, const float *eta, const int32_t *searching,
                               float *z, float *part, const int32_t *skip, hipStream_t s);
-// objective of the trial point: the sum of the frows rows of fpart
-hipError_t launch_fista_accept(int n, int B, int frows, const float *fpart, const float *part, const float *Fy, float *eta,
-                               int32_t *searching, float *Fout, int last, int32_t *pending, const int32_t *skip,
-                               hipStream_t s);
+// objective of the trial point: the sum of the frows rows of fpart (summed: of
+// the first level's results)
+hipError_t launch_fista_accept(int n, int B, int frows, bool summed, const float *fpart, const float *part,
+                               const float *Fy, float *eta, int32_t *searching, float *Fout, int last, int32_t *pending,
+                               const int32_t *skip, hipStream_t s);
 hipError_t launch_fista_finish(int n, int B, const int32_t *active, float *t, float *coef, const float *z, float *x,
                                float *y, hipStream_t s);
 

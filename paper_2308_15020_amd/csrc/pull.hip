@@ -153,7 +153,9 @@ __global__ __launch_bounds__(64 * PULL_WAVES) void k_pull(PullArgs a, const floa
                         }
                     }
                 }
-                const float wc1 = wc * c1;
+                // a null entry reads the weight of constraint 0, which a caller may
+                // have set to an infinity or NaN
+                const float wc1 = rk == RK_NULL ? 0.f : wc * c1;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
                     const float gterm = wc1 * prod[r];

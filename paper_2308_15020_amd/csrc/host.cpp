@@ -1374,7 +1374,9 @@ static std::vector<int2> xcd_order(std::vector<Blk> &blk)
 }
 
 // Block table of the FP64-arithmetic root-of-unity bins of evaluation io (of the
-// FP32 evaluation only under a grouped launch structure).  Measured on constraints
+// FP32 evaluation only under a grouped launch structure).  That of the FP64
+// evaluation depends on nothing that the tuner changes: it is built with the plan
+// and stays, so that launches captured by the caller keep their table.  Measured on constraints
 // of every length in FP64 (300 at-least-t among 2100, 201 restarts): 640 -> 279 us
 // against a launch per bin, 38 of them too small to fill the chip.
 static ffsat_status build_group64(ffsat_plan *pl, int io)
@@ -1423,7 +1425,8 @@ static ffsat_status build_group64(ffsat_plan *pl, int io)
 // frequencies over 4 waves (fg = 4).  Blocks are ordered longest first
 // (estimated VALU work), with the real-chain blocks spread evenly among the
 // root-of-unity ones so that every CU mixes memory- and ALU-bound waves.
-// The FP64-arithmetic root-of-unity bins have block tables of their own.
+// The FP64-arithmetic root-of-unity bins have block tables of their own (that
+// of the FP32 evaluation is built here too).
 static ffsat_status build_groups(ffsat_plan *pl)
 {
     (void)hipFree(pl->d_gent);
@@ -1433,10 +1436,8 @@ static ffsat_status build_groups(ffsat_plan *pl)
     pl->gblocks = 0;
     pl->glds = 0;
     pl->gsolo.clear();
-    for (int io : {IO_F32, IO_F64}) {
-        const ffsat_status st = build_group64(pl, io);
-        if (st != FFSAT_OK) return st;
-    }
+    const ffsat_status st = build_group64(pl, IO_F32);
+    if (st != FFSAT_OK) return st;
     if (!pl->grouped) return FFSAT_OK;
     const std::vector<Bin> &bins = pl->bins[IO_F32];
     std::vector<GroupEntry> ent;
@@ -2166,6 +2167,7 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
                 pl->persistent_class = cmin;
         }
     }
+    if (st == FFSAT_OK) st = build_group64(pl, IO_F64);
     if (st == FFSAT_OK) st = build_groups(pl);
     if (st == FFSAT_OK && opts && opts->autotune) {
         st = ffsat_plan_tune(pl, nullptr);

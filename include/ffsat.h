@@ -133,7 +133,9 @@ typedef struct {
                                 per-literal slots and the slot reduction, 2 gathered
                                 per variable for lengths <= 7, 3 for lengths <= 3
                                 (the pulled gradient; never with a fixed launch
-                                structure 2, never for n * B above 2^29); reserved[3]:
+                                structure 2, never for n * B above 2^29 or more than
+                                2^29 - 17 (lengths <= 3) or 2^28 - 9 pulled
+                                literals); reserved[3]:
                                 variables per wave of the pulled gradient, 0..8
                                 (0: 1, or 2 from n = 32768 on); reserved[4] = 1: ffsat_run_steps and
                                 ffsat_run_iters run all T iterations in one

@@ -1833,10 +1833,9 @@ static ffsat_status set_pull(ffsat_plan *pl, int c)
         if (!mid) c = PULL_LE3;
     }
     if (c != PULL_OFF) {
-        bool any = false;
-        for (const Bin &b : pl->bins[IO_F32]) any = any || b.pk >= c;
-        // k_pull's gathers are buffer loads with 31-bit offsets into x
-        const bool fits = (int64_t)pl->p->n * pl->B * 4 <= 0x7fffffffll;
+        int64_t lits = 0;
+        for (const Bin &b : pl->p->lay[IO_F32].bins) lits += b.pk >= c ? b.lits : 0;
+        const bool any = lits > 0, fits = pull_fits(pl->p->n, pl->B, lits, PULL_E[c]);
         const bool held = pl->mode == MODE_GROUP_ALL && !(pl->mode_auto && pull_all_class(pl) >= c);
         if (!any || !fits || held) c = PULL_OFF;
     }

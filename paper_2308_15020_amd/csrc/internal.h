@@ -135,6 +135,13 @@ struct Bin {
 enum { PULL_OFF = 0, PULL_LE7 = 1, PULL_LE3 = 2 };
 constexpr int PULL_K[3] = {0, 7, 3};
 constexpr int PULL_E[3] = {0, 8, 4};
+// What k_pull can index: gathers are buffer loads with 31-bit byte offsets into
+// the points, entries of `lits` pulled literals are read at 32-bit word indexes
+// (and a batch of 64 words past the last).
+inline bool pull_fits(int64_t n, int64_t B, int64_t lits, int E)
+{
+    return n * B * 4 <= 0x7fffffffll && lits * E + 64 <= 0x7fffffffll;
+}
 constexpr int PULL_VC_MAX = 8;   // most variables per wave of k_pull
 constexpr int PULL_WAVES = 4;    // waves per block of k_pull, which share an objective / count row
 

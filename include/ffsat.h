@@ -182,7 +182,11 @@ ffsat_status ffsat_get_weights(const ffsat_problem *p, float *w, int32_t on_devi
 
 /* Binds the batch size B >= 1 and allocates the workspace (per-literal slot
  * buffer of nnz*B values, objective partials).  opts may be NULL (no
- * autotuning, graphs on).  *out is written only on success. */
+ * autotuning, graphs on).  *out is written only on success.
+ * A plan whose gradient is gathered by default (reserved[2] = 0, without the
+ * autotuner) allocates the lists (kept with the problem) and the second point
+ * buffer of n*B values for it at its first gradient or step that is not under
+ * stream capture; until then, and where they do not fit, the slots serve. */
 ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffsat_plan_opts *opts,
                                ffsat_plan **out);
 ffsat_status ffsat_plan_destroy(ffsat_plan *plan);

@@ -118,7 +118,8 @@ class Plan:
         o.reserved[1] = modes[mode]
         # gradient of the short transform-free constraints gathered per variable
         # ("le3": length <= 3, "le7": <= 7) instead of through slots ("off");
-        # "auto": chosen by the autotuner (off without it)
+        # "auto": chosen by the autotuner (without it "le3" where every constraint
+        # has at most three literals, else off)
         pulls = {"auto": 0, "off": 1, "le7": 2, "le3": 3}
         if pull not in pulls:
             raise ValueError(f"pull must be one of {sorted(pulls)}")

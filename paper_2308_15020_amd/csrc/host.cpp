@@ -715,6 +715,16 @@ static ffsat_status validate(const ffsat_problem_desc *d)
     return FFSAT_OK;
 }
 
+static void free_pull(PullLayout &P)
+{
+    (void)hipFree(P.d_pptr);
+    (void)hipFree(P.d_pent);
+    (void)hipFree(P.d_vptr);
+    (void)hipFree(P.d_vslot);
+    (void)hipFree(P.d_rk);
+    P = PullLayout();
+}
+
 static void free_layout(Layout &L)
 {
     (void)hipFree(L.d_con);
@@ -726,13 +736,7 @@ static void free_layout(Layout &L)
     (void)hipFree(L.d_t64);
     (void)hipFree(L.d_f32);
     (void)hipFree(L.d_f64);
-    for (PullLayout &P : L.pull) {
-        (void)hipFree(P.d_pptr);
-        (void)hipFree(P.d_pent);
-        (void)hipFree(P.d_vptr);
-        (void)hipFree(P.d_vslot);
-        (void)hipFree(P.d_rk);
-    }
+    for (PullLayout &P : L.pull) free_pull(P);
     L = Layout();
 }
 
@@ -743,6 +747,7 @@ static void free_layout(Layout &L)
 // variable-major transpose of every other slot.  Built once per class.
 static ffsat_status build_pull(ffsat_problem *p, int c)
 {
+    std::lock_guard<std::mutex> lk(p->pull_mu);
     Layout &Ly = p->lay[IO_F32];
     PullLayout &P = Ly.pull[c];
     if (P.built) return FFSAT_OK;
@@ -788,11 +793,16 @@ static ffsat_status build_pull(ffsat_problem *p, int c)
         }
     }
     ffsat_status st;
-    if ((st = upload(&P.d_pptr, pptr, p->device_bytes)) != FFSAT_OK) return st;
-    if (!pent.empty() && (st = upload(&P.d_pent, pent, p->device_bytes)) != FFSAT_OK) return st;
-    if ((st = upload(&P.d_vptr, vptr, p->device_bytes)) != FFSAT_OK) return st;
-    if (!vslot.empty() && (st = upload(&P.d_vslot, vslot, p->device_bytes)) != FFSAT_OK) return st;
-    if ((st = upload(&P.d_rk, rkind_table(), p->device_bytes)) != FFSAT_OK) return st;
+    const int64_t held = p->device_bytes;
+    if ((st = upload(&P.d_pptr, pptr, p->device_bytes)) != FFSAT_OK ||
+        (!pent.empty() && (st = upload(&P.d_pent, pent, p->device_bytes)) != FFSAT_OK) ||
+        (st = upload(&P.d_vptr, vptr, p->device_bytes)) != FFSAT_OK ||
+        (!vslot.empty() && (st = upload(&P.d_vslot, vslot, p->device_bytes)) != FFSAT_OK) ||
+        (st = upload(&P.d_rk, rkind_table(), p->device_bytes)) != FFSAT_OK) {
+        free_pull(P);
+        p->device_bytes = held;
+        return st;
+    }
     P.n_ent = pptr[(size_t)n];
     P.n_rest = vptr[(size_t)n];
     for (int64_t e = 0; e < P.n_ent; ++e) P.n_gather += ((pent[(size_t)e * E + 1] >> 3) & 7);
@@ -1853,6 +1863,33 @@ static ffsat_status set_pull(ffsat_plan *pl, int c)
     return FFSAT_OK;
 }
 
+// The first gradient or step of a plan that takes the pull path by default
+// (ffsat_plan_create) brings its lists and second point buffer.  The slots stay
+// where there is no memory for them, and for a call under capture, which must
+// not allocate: everything they need is there from the plan's creation.
+static void take_pull(ffsat_plan *pl, hipStream_t s)
+{
+    if (pl->pull_later == PULL_OFF) return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();   // the null stream while another one captures
+        return;
+    }
+    const int c = pl->pull_later;
+    pl->pull_later = PULL_OFF;
+    const std::string msg = g_last_error;
+    ffsat_status st;
+    try {
+        st = set_pull(pl, c);
+    } catch (const std::bad_alloc &) {
+        st = FFSAT_E_NOMEM;
+    }
+    if (st != FFSAT_OK) {
+        (void)hipGetLastError();
+        g_last_error = msg;
+    }
+}
+
 static hipError_t enqueue_iters(ffsat_plan *pl, float *x, int T, bool erwa, float *F, int32_t *n_sat, int32_t *U,
                                 hipStream_t s);
 static hipError_t enqueue_iters_overlapped(ffsat_plan *pl, float *x, int T, bool erwa, float *F,
@@ -1994,6 +2031,7 @@ extern "C" ffsat_status ffsat_plan_tune(ffsat_plan *pl, void *stream)
     hipStream_t s = (hipStream_t)stream;
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
+    pl->pull_later = PULL_OFF;   // timed and chosen here
     const ffsat_problem *p = pl->p;
     if (!pl->d_scratch_x) {
         HIPCHK(hipMalloc(&pl->d_scratch_x, sizeof(float) * (size_t)p->n * (size_t)pl->B));
@@ -2143,12 +2181,14 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
             if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
         if (e != hipSuccess) st = fail(FFSAT_E_HIP, "side streams: %s", hipGetErrorString(e));
     }
-    // every constraint of at most three literals: gathered from the start, one
-    // launch a step instead of two and no slots (3-SAT, n = 250 at 1024 restarts 22
+    // every constraint of at most three literals: gathered, one launch a step
+    // instead of two and no slots written or read (3-SAT, n = 250 at 1024 restarts 22
     // -> 14 us per step, n = 10000 at 256 88 -> 44, n = 100000 at 256 1030 -> 480).
     // Longer ones gather k - 1 points per literal and do not always win (OR of
     // 3..7, n = 2000: 31 -> 36 us at 256 restarts, 90 -> 74 at 1024): the tuner's choice.
-    if (st == FFSAT_OK && pl->pull_auto && pl->mode_auto && pull_all_class(pl) == PULL_LE3) st = set_pull(pl, PULL_LE3);
+    // A plan that only checks needs none of it: see take_pull.
+    if (pl->pull_auto && pl->mode_auto && pull_all_class(pl) == PULL_LE3 && pull_fits(p->n, B, p->nnz, PULL_E[PULL_LE3]))
+        pl->pull_later = PULL_LE3;
     if (st == FFSAT_OK && !pl->pull_auto) st = set_pull(pl, preq == 1 ? PULL_OFF : (preq == 2 ? PULL_LE7 : PULL_LE3));
     if (st == FFSAT_OK && pl->persistent) {
         // eligible: every constraint pulled (transform-free, length <= 7) and
@@ -2277,19 +2317,29 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
 {
     if (!pl || !buf || len == 0) return fail(FFSAT_E_INVALID_ARG, "NULL argument");
     std::ostringstream o;
+    // the class that gradients and steps take; its lists' sizes once they are there
+    const int pull = pl->pull_later ? pl->pull_later : pl->pull;
+    int64_t n_ent = 0, n_gather = 0, n_rest = 0;
+    if (pull) {
+        std::lock_guard<std::mutex> lk(pl->p->pull_mu);
+        const PullLayout &P = pl->p->lay[IO_F32].pull[pull];
+        n_ent = P.n_ent;
+        n_gather = P.n_gather;
+        n_rest = P.n_rest;
+    }
     static const char *mode_names[] = {"auto", "per_bin", "group_all", "group_dft"};
     o << "{\"B\": " << pl->B << ", \"tuned\": " << (pl->tuned ? "true" : "false") << ", \"mode\": \""
       << mode_names[pl->mode] << "\"" << ", \"mode_auto\": " << (pl->mode_auto ? "true" : "false")
       << ", \"grouped\": " << (pl->grouped && pl->gblocks > 0 ? "true" : "false") << ", \"group_blocks\": " << pl->gblocks
       << ", \"group64_blocks\": " << pl->gblocks64[IO_F32] << ", \"solo_bins\": " << pl->gsolo.size() << ", \"graphs_cached\": " << pl->graphs.size()
-      << ", \"graph_captures\": " << pl->captures << ", \"pull\": " << PULL_K[pl->pull]
+      << ", \"graph_captures\": " << pl->captures << ", \"pull\": " << PULL_K[pull]
       << ", \"pull_auto\": " << (pl->pull_auto ? "true" : "false") << ", \"pull_vc\": " << pl->pull_vc
-      << ", \"pull_entries\": " << (pl->pull ? pl->p->lay[IO_F32].pull[pl->pull].n_ent : 0)
-      << ", \"pull_entry_bytes\": " << (pl->pull ? 4 * PULL_E[pl->pull] : 0)
-      << ", \"pull_gathers_per_restart\": " << (pl->pull ? pl->p->lay[IO_F32].pull[pl->pull].n_gather : 0)
-      << ", \"pull_other_slots\": " << (pl->pull ? pl->p->lay[IO_F32].pull[pl->pull].n_rest : 0)
-      << ", \"pull_rows\": " << (pl->pull ? pull_rows(pl) : 0) << ", \"pull_rpl\": " << pl->pull_rpl
-      << ", \"objective_rows\": " << eval_rows(pl, IO_F32, pl->pull)
+      << ", \"pull_entries\": " << n_ent
+      << ", \"pull_entry_bytes\": " << (pull ? 4 * PULL_E[pull] : 0)
+      << ", \"pull_gathers_per_restart\": " << n_gather
+      << ", \"pull_other_slots\": " << n_rest
+      << ", \"pull_rows\": " << (pull ? pull_rows(pl) : 0) << ", \"pull_rpl\": " << pl->pull_rpl
+      << ", \"objective_rows\": " << eval_rows(pl, IO_F32, pull)
       << ", \"group_real_cpw\": " << pl->group_real_cpw << ", \"group_dft_fg\": " << pl->group_dft_fg
       << ", \"tuned_modes\": [" << pl->tune_log << "], \"persistent_steps\": "
       << (pl->persistent_class ? "true" : "false") << ", \"bins\": {";
@@ -2303,7 +2353,7 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
               << ", \"lits\": " << b.lits << ", \"cost\": " << b.cost << ", \"flops_per_restart\": " << b.flops
               << ", \"bytes_per_restart\": " << b.bytes << ", \"positions_per_restart\": " << b.exec_pos
               << ", \"k2_per_restart\": " << b.k2 << ", \"alg_flops_per_restart\": " << b.alg
-              << ", \"pull_class\": " << b.pk << ", \"pulled\": " << (io == IO_F32 && pl->pull && b.pk >= pl->pull ? "true" : "false")
+              << ", \"pull_class\": " << b.pk << ", \"pulled\": " << (io == IO_F32 && pull && b.pk >= pull ? "true" : "false")
               << ", \"cpw\": " << b.cpw
               << ", \"wpb\": " << b.wpb << ", \"fg\": " << b.fg;
             // the grouped launch that evaluates the bin, if any
@@ -2529,6 +2579,7 @@ extern "C" ffsat_status ffsat_eval(ffsat_plan *pl, const float *x, float *F, flo
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
     if (!F && !grad && !con_val) return FFSAT_OK;
+    if (grad && !con_val) take_pull(pl, s);
     return run_eval<float>(pl, x, F, grad, con_val, nullptr, nullptr, nullptr, nullptr, 0.f, s);
 }
 
@@ -2541,6 +2592,7 @@ extern "C" ffsat_status ffsat_eval_check(ffsat_plan *pl, const float *x, float *
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
     if (!F && !grad && !con_val) return run_check<float>(pl, x, nullptr, n_sat, unsat_bits, U, s);
+    if (grad && !con_val) take_pull(pl, s);
     return run_eval<float>(pl, x, F, grad, con_val, n_sat, unsat_bits, U, nullptr, 0.f, s);
 }
 
@@ -2552,6 +2604,7 @@ extern "C" ffsat_status ffsat_eval_step(ffsat_plan *pl, float *x, float eta, flo
     ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
     if ((st = check_finite<float>(pl, x, s)) != FFSAT_OK) return st;
+    take_pull(pl, s);
     return run_eval<float>(pl, x, F, nullptr, nullptr, n_sat, nullptr, U, x, eta, s);
 }
 
@@ -2713,6 +2766,7 @@ extern "C" ffsat_status ffsat_run_steps(ffsat_plan *pl, float *x, int32_t T, flo
         HIPCHK(enqueue_iters_small(pl, x, T, F_last, nullptr, nullptr, eta, 0.f, s));
         return FFSAT_OK;
     }
+    take_pull(pl, s);
     // the step size goes to device memory ahead of the (captured) steps
     HIPCHK(launch_set_f32x2(pl->d_hyper, eta, 0.f, s));
     if (!pl->use_graphs) {
@@ -2840,6 +2894,7 @@ extern "C" ffsat_status ffsat_run_iters(ffsat_plan *pl, float *x, int32_t T, flo
         HIPCHK(enqueue_iters_small(pl, x, T, F, n_sat, U, eta, alpha, s));
         return FFSAT_OK;
     }
+    take_pull(pl, s);
     // step size and rate go to device memory ahead of the (captured) iterations
     HIPCHK(launch_set_f32x2(pl->d_hyper, eta, alpha, s));
     auto body = [&](hipStream_t cs) {

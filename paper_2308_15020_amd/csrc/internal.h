@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <map>
+#include <mutex>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -209,6 +210,9 @@ struct ffsat_problem {
     int32_t n_long = 0;
     ffsat::Layout lay[2];
     int64_t device_bytes = 0;
+    // the lists of Layout::pull are built when a plan first needs them; plans of
+    // one problem may do so from several threads
+    std::mutex pull_mu;
     // host copy of the constraint set (original order)
     std::vector<int64_t> h_con_ptr;
     std::vector<int32_t> h_lits, h_kinds, h_params;
@@ -336,6 +340,7 @@ struct ffsat_plan {
     // chosen by the tuner unless fixed by the options)
     int pull = 0;
     bool pull_auto = false;
+    int pull_later = 0;              // class taken at the first gradient or step (take_pull)
     int pull_vc = 8;                 // variables per wave of k_pull
     int pull_rpl = 4;                // 64-restart blocks per wave of k_pull
     bool persistent = false;         // ffsat_run_steps as one persistent launch (small all-pulled problems)

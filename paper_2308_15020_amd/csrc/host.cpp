@@ -1209,7 +1209,10 @@ static ffsat_status ensure_workspace(ffsat_plan *pl, int io)
     // variable chunk of the pulled gradient
     const int max_rows = pl->p->m + pl->p->n;
     const size_t slot = (size_t)pl->p->nnz * B * es;
-    const size_t fpart = (size_t)max_rows * B * es;
+    // the packed signs of the exact check alone take the FP32 objective rows'
+    // place (run_check): smaller from two restarts on, n / 8 bytes a restart
+    const size_t signs = io == IO_F32 ? sizeof(uint64_t) * (size_t)pl->p->n * (size_t)sign_stride(pl->B) : 0;
+    const size_t fpart = std::max((size_t)max_rows * B * es, signs);
     const size_t ftmp = (size_t)f_splits(max_rows) * B * es;
     HIPCHK(hipMalloc(&pl->d_slot[io], slot));
     HIPCHK(hipMalloc(&pl->d_fpart[io], fpart));
@@ -2164,9 +2167,6 @@ extern "C" ffsat_status ffsat_plan_create(ffsat_problem *p, int32_t B, const ffs
         hipError_t e = hipMalloc(&pl->d_flag, sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&pl->d_umax, 1024 * sizeof(int32_t));
         if (e == hipSuccess) e = hipMalloc(&pl->d_hyper, 2 * sizeof(float));
-        const size_t signs = sizeof(uint64_t) * (size_t)p->n * (size_t)sign_stride(B);
-        if (e == hipSuccess) e = hipMalloc(&pl->d_signs, signs);
-        pl->device_bytes += (int64_t)signs;
         if (e != hipSuccess) st = fail(FFSAT_E_NOMEM, "hipMalloc flag: %s", hipGetErrorString(e));
     }
     if (st == FFSAT_OK && !(opts && opts->reserved[0] == 1)) {
@@ -2288,7 +2288,6 @@ extern "C" ffsat_status ffsat_plan_destroy(ffsat_plan *pl)
     (void)hipFree(pl->d_umax);
     (void)hipFree(pl->d_cpart);
     (void)hipFree(pl->d_ctmp);
-    (void)hipFree(pl->d_signs);
     (void)hipFree(pl->d_scratch_x);
     (void)hipFree(pl->d_fz);
     (void)hipFree(pl->d_fg);
@@ -2328,7 +2327,7 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
         n_rest = P.n_rest;
     }
     static const char *mode_names[] = {"auto", "per_bin", "group_all", "group_dft"};
-    o << "{\"B\": " << pl->B << ", \"tuned\": " << (pl->tuned ? "true" : "false") << ", \"mode\": \""
+    o << "{\"B\": " << pl->B << ", \"device_bytes\": " << pl->device_bytes << ", \"tuned\": " << (pl->tuned ? "true" : "false") << ", \"mode\": \""
       << mode_names[pl->mode] << "\"" << ", \"mode_auto\": " << (pl->mode_auto ? "true" : "false")
       << ", \"grouped\": " << (pl->grouped && pl->gblocks > 0 ? "true" : "false") << ", \"group_blocks\": " << pl->gblocks
       << ", \"group64_blocks\": " << pl->gblocks64[IO_F32] << ", \"solo_bins\": " << pl->gsolo.size() << ", \"graphs_cached\": " << pl->graphs.size()
@@ -2483,7 +2482,9 @@ static ReduceArgs<IO> reduce_args(ffsat_plan *pl, int io, IO *grad, float *x_ste
 }
 
 // The exact check alone (and the assignment bits): signs packed, then the
-// constraints on the packed signs.
+// constraints on the packed signs.  Points of either type take the workspace of
+// the plan's creation: the signs in place of the FP32 objective rows, which a
+// check does not write.
 template <typename IO>
 static ffsat_status run_check(ffsat_plan *pl, const IO *x, uint32_t *assign_bits, int32_t *n_sat, uint32_t *unsat_bits,
                               int32_t *U, hipStream_t s)
@@ -2492,14 +2493,15 @@ static ffsat_status run_check(ffsat_plan *pl, const IO *x, uint32_t *assign_bits
     const Layout &Ly = p->lay[IO_F32];   // any layout holds the constraints; points of either type
     const bool check = n_sat || unsat_bits || U;
     if (!check && !assign_bits) return FFSAT_OK;
-    if constexpr (sizeof(IO) == 4) HIPCHK(launch_signs_f32(p->n, pl->B, x, pl->d_signs, assign_bits, s));
-    else HIPCHK(launch_signs_f64(p->n, pl->B, x, pl->d_signs, assign_bits, s));
+    uint64_t *signs = (uint64_t *)pl->d_fpart[IO_F32];
+    if constexpr (sizeof(IO) == 4) HIPCHK(launch_signs_f32(p->n, pl->B, x, signs, assign_bits, s));
+    else HIPCHK(launch_signs_f64(p->n, pl->B, x, signs, assign_bits, s));
     if (!check) return FFSAT_OK;
     CheckArgs a{};
     a.con = Ly.d_con;
     a.pos = Ly.d_pos;
     a.lit = Ly.d_lit;
-    a.signs = pl->d_signs;
+    a.signs = signs;
     a.unsat_bits = unsat_bits;
     a.U = U;
     a.rows = n_sat ? pl->d_cpart : nullptr;
@@ -2935,7 +2937,7 @@ extern "C" ffsat_status ffsat_round_check_f64(ffsat_plan *pl, const double *x, u
 {
     if (!pl || !x) return fail(FFSAT_E_INVALID_ARG, "NULL plan or x");
     hipStream_t s = (hipStream_t)stream;
-    ffsat_status st = ensure_workspace(pl, IO_F64);
+    ffsat_status st = ensure_workspace(pl, IO_F32);
     if (st != FFSAT_OK) return st;
     return run_check<double>(pl, x, assign_bits, n_sat, unsat_bits, U, s);
 }

@@ -294,7 +294,6 @@ struct ffsat_plan {
     void *d_ftmp[2] = {nullptr, nullptr};
     int32_t *d_cpart = nullptr;      // violated-count rows (shared by both precisions)
     int32_t *d_ctmp = nullptr;
-    uint64_t *d_signs = nullptr;     // [n][sign_stride(B)] packed signs of the exact check alone
     int fpart_rows[2] = {0, 0};
     int32_t *d_flag = nullptr;       // debug non-finite flag
     int32_t *d_umax = nullptr;       // [1024] partial maxima of the weight update

@@ -1346,11 +1346,14 @@ static void prof_end(ffsat_plan *pl, hipStream_t s, ProfRec &r)
 }
 
 // Root-of-unity bins with FP64 arithmetic that the FP64 grouped launch of
-// evaluation io can hold.
-static bool in_group64(const Bin &b, int io)
+// evaluation io has a kernel for, whatever their present shape.
+static bool can_group64(const Bin &b, int io)
 {
-    return !b.uc && b.ct == CT_F64 && b.cls == CLASS_DFT && (b.fg == 1 || b.fg == 4) && group_variant64(io, b.seg, b.L) >= 0;
+    return !b.uc && b.ct == CT_F64 && b.cls == CLASS_DFT && group_variant64(io, b.seg, b.L) >= 0;
 }
+// Those that it holds: a grouped block is four units, or one over four waves (a
+// per-bin shape may split the frequencies over two).
+static bool in_group64(const Bin &b, int io) { return can_group64(b, io) && (b.fg == 1 || b.fg == 4); }
 
 struct Blk {
     int2 b;         // entry, first unit
@@ -1717,7 +1720,7 @@ constexpr int GROUP_DFT_FG = 1;
 constexpr int GROUP_CODE_MAX = 8 * 64 + 7;   // cache code of the grouped shapes: 8 * chain cpw + fg
 static bool in_group(const ffsat_plan *pl, const Bin &b)
 {
-    if (in_group64(b, IO_F32)) return true;
+    if (can_group64(b, IO_F32)) return true;
     if (b.uc || group_variant(b.ct, b.cls, b.seg, b.L, b.cnt) < 0) return false;
     return b.cls == CLASS_DFT || pl->mode == MODE_GROUP_ALL;
 }

@@ -1394,7 +1394,9 @@ static std::vector<int2> xcd_order(std::vector<Blk> &blk)
 // evaluation depends on nothing that the tuner changes: it is built with the plan
 // and stays, so that launches captured by the caller keep their table.  Measured on constraints
 // of every length in FP64 (300 at-least-t among 2100, 201 restarts): 640 -> 279 us
-// against a launch per bin, 38 of them too small to fill the chip.
+// against a launch per bin, 38 of them too small to fill the chip.  A single bin
+// of the FP64 evaluation keeps its own launch, which does not look up a block (one
+// constraint of 100 literals, 1 restart: 18 us grouped, 16 by itself).
 static ffsat_status build_group64(ffsat_plan *pl, int io)
 {
     (void)hipFree(pl->d_gent64[io]);
@@ -1424,7 +1426,10 @@ static ffsat_status build_group64(ffsat_plan *pl, int io)
         }
         row0 += rows;
     }
-    if (ent.empty()) return FFSAT_OK;
+    if (ent.empty() || (io == IO_F64 && ent.size() < 2)) {
+        pl->glds64[io] = 0;
+        return FFSAT_OK;
+    }
     const std::vector<int2> order = xcd_order(blk);
     HIPCHK(hipMalloc(&pl->d_gent64[io], ent.size() * sizeof(GroupEntry)));
     HIPCHK(hipMemcpy(pl->d_gent64[io], ent.data(), ent.size() * sizeof(GroupEntry), hipMemcpyHostToDevice));
@@ -1754,10 +1759,20 @@ static void set_group_shapes(ffsat_plan *pl, int c, int f)
     pl->fpart_rows[IO_F32] = fpart_rows_of(bins);
 }
 
+// FP64 evaluation: units of all its root-of-unity bins up to which their
+// frequencies are split, a block per CU.  One wave against four a unit, at-least-t of 100 literals, us: 64
+// units (1 restart) 31 / 23, 256 (16 restarts) 32 / 26, 512 (16) 35 / 32, 1024
+// (64) 36 / 42; of 512 literals: 64 units 49 / 40, 256 56 / 45, 512 62 / 64, 1024
+// 66 / 99.  Below 32 literals there is nothing to split (20: 19 / 21).
+constexpr int64_t F64_SPLIT_UNITS = 256;
+
 // Constraints per wave: enough waves per bin to cover the chip (the
 // autotuner refines this).  Root-of-unity bins keep one constraint per wave.
 static void default_shapes(ffsat_plan *pl)
 {
+    int64_t f64_units = 0;
+    for (const Bin &b : pl->bins[IO_F64])
+        if (can_group64(b, IO_F64)) f64_units += (int64_t)b.count * ((pl->B + (64 / b.L) - 1) / (64 / b.L));
     for (int io = 0; io < 2; ++io) {
         for (Bin &b : pl->bins[io]) {
             b.wpb = 4;
@@ -1767,8 +1782,9 @@ static void default_shapes(ffsat_plan *pl)
                 // waves until the bin alone has about 3 waves per SIMD
                 b.cpw = 1;
                 if (b.cnt) continue;
-                if (io == IO_F64 && !b.uc && group_variant64(io, b.seg, b.L) >= 0) {
-                    b.fg = 1;   // one grouped launch: it fills the chip by itself
+                if (io == IO_F64 && can_group64(b, io)) {
+                    // one grouped launch: split where it leaves CUs without a block
+                    b.fg = b.maxk >= 32 && f64_units <= F64_SPLIT_UNITS ? 4 : 1;
                 } else if (pl->grouped) {
                     // the grouped launch fills the chip anyway: split the
                     // frequencies of long constraints only (fg 1 or 4)

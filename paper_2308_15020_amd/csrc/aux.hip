@@ -19,37 +19,41 @@ static constexpr int F_ROWS_PER_SPLIT = 64;
 
 int f_splits(int rows) { return (rows + F_ROWS_PER_SPLIT - 1) / F_ROWS_PER_SPLIT; }
 
-// Grid: x = VEC variables, then one block per split of objective rows; y = chunk
-// of RED_BLOCK restarts.  A wave has one variable (the transpose is read with
-// scalar loads) and 64 VEC restarts.  VEC values per access, up to 16 bytes where
-// the rows allow it (B a multiple of VEC, buffers aligned): 1000 variables, 10000
-// restarts 85 us with single values, 57 with four (256 MB of slots: 4.9 TB/s);
-// mixed n = 2000, 1024 restarts 44 -> 42.
+// Grid: x = VEC variables (with copy_src an equal share of the points, as one run
+// of values), then one block per split of objective rows; y = chunk of RED_BLOCK
+// restarts.  A wave has one variable (the transpose is read with scalar loads)
+// and 64 VEC restarts.  VEC values per access, up to 16 bytes where the rows allow
+// it (B a multiple of VEC, buffers aligned): 1000 variables, 10000 restarts 85 us
+// with single values, 57 with four (256 MB of slots: 4.9 TB/s); mixed n = 2000,
+// 1024 restarts 44 -> 42.  The copy by variables left lanes idle at few restarts
+// (100000 variables, 1 restart: a step 193 us, now 171).
 template <typename T, int VEC>
 struct alignas(sizeof(T) * VEC) VecT {
     T v[VEC];
 };
 template <typename IO, bool STEP, int VEC>
-__global__ __launch_bounds__(RED_BLOCK) void k_reduce(ReduceArgs<IO> a, int n_grad)
+__global__ __launch_bounds__(RED_BLOCK) void k_reduce(ReduceArgs<IO> a, int splits)
 {
     const int bx = blockIdx.x;
     if (a.skip != nullptr && *a.skip == 0) return;
     const int B = a.B;
     constexpr int WPV = RED_BLOCK / (64 * VEC);   // waves that share a variable
-    const int gblocks = (n_grad + VEC - 1) / VEC;
+    const int gblocks = (int)gridDim.x - splits;
     if (bx < gblocks) {
-        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const int v = bx * VEC + wave / WPV;
-        const int b = (int)blockIdx.y * RED_BLOCK + ((wave % WPV) * 64 + (int)(threadIdx.x & 63)) * VEC;
-        if (v >= n_grad || b >= B) return;
         using V = VecT<IO, VEC>;
         if constexpr (!STEP) {
             if (a.copy_src != nullptr) {
-                const size_t i = (size_t)v * B + b;
-                *reinterpret_cast<V *>(&a.copy_dst[i]) = *reinterpret_cast<const V *>(&a.copy_src[i]);
+                // the points as one run of values, whatever the rows' length
+                const int64_t i = (((int64_t)blockIdx.y * gblocks + bx) * RED_BLOCK + (int)threadIdx.x) * VEC;
+                if (i < (int64_t)a.n * B)
+                    *reinterpret_cast<V *>(&a.copy_dst[i]) = *reinterpret_cast<const V *>(&a.copy_src[i]);
                 return;
             }
         }
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int v = bx * VEC + wave / WPV;
+        const int b = (int)blockIdx.y * RED_BLOCK + ((wave % WPV) * 64 + (int)(threadIdx.x & 63)) * VEC;
+        if (v >= a.n || b >= B) return;
         const int e0 = a.vptr[v], e1 = a.vptr[v + 1];
         double acc[VEC] = {};
         int e = e0;
@@ -166,18 +170,20 @@ template <typename IO, bool STEP>
 static hipError_t reduce_impl(const ReduceArgs<IO> &a, hipStream_t s, int parts = 3)
 {
     const bool want_g = STEP ? (a.x_step != nullptr) : (a.grad != nullptr || a.copy_src != nullptr);
-    const int n_grad = want_g ? a.n : 0;
+    const int chunks = (a.B + RED_BLOCK - 1) / RED_BLOCK;
     const bool rows = a.F != nullptr || a.n_sat != nullptr;
     const int splits = rows ? f_splits(a.rows) : 0;
-    if ((parts & 1) && n_grad + splits > 0) {
+    if ((parts & 1) && (want_g || splits > 0)) {
         const auto fits = [&](int vec) {
             const auto al = [&](const void *p) { return ((uintptr_t)p & (sizeof(IO) * (size_t)vec - 1)) == 0; };
             return a.B % vec == 0 && al(a.slot) && al(a.grad) && al(a.x_step) && al(a.copy_src) && al(a.copy_dst);
         };
         const auto go = [&](auto vec) {
             constexpr int VEC = decltype(vec)::value;
-            const dim3 grid((unsigned)((n_grad + VEC - 1) / VEC + splits), (unsigned)((a.B + RED_BLOCK - 1) / RED_BLOCK));
-            hipLaunchKernelGGL((k_reduce<IO, STEP, VEC>), grid, dim3(RED_BLOCK), 0, s, a, n_grad);
+            const int64_t share = (int64_t)RED_BLOCK * VEC * chunks;
+            const int64_t gblocks = !want_g ? 0 : (a.copy_src ? ((int64_t)a.n * a.B + share - 1) / share : (a.n + VEC - 1) / VEC);
+            hipLaunchKernelGGL((k_reduce<IO, STEP, VEC>), dim3((unsigned)(gblocks + splits), (unsigned)chunks), dim3(RED_BLOCK),
+                               0, s, a, splits);
         };
         constexpr int MOST = 16 / (int)sizeof(IO);
         if (MOST == 4 && fits(4)) go(std::integral_constant<int, MOST>{});

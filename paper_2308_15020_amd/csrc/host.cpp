@@ -1760,10 +1760,11 @@ static void set_group_shapes(ffsat_plan *pl, int c, int f)
 }
 
 // FP64 evaluation: units of all its root-of-unity bins up to which their
-// frequencies are split, a block per CU.  One wave against four a unit, at-least-t of 100 literals, us: 64
-// units (1 restart) 31 / 23, 256 (16 restarts) 32 / 26, 512 (16) 35 / 32, 1024
-// (64) 36 / 42; of 512 literals: 64 units 49 / 40, 256 56 / 45, 512 62 / 64, 1024
-// 66 / 99.  Below 32 literals there is nothing to split (20: 19 / 21).
+// frequencies are split, a block per CU.  One wave against four a unit,
+// at-least-t of 100 literals, us: 64 units (1 restart) 31 / 23, 256 (16
+// restarts) 32 / 26, 512 (16) 35 / 32, 1024 (64) 36 / 42; of 512 literals: 64 units
+// 49 / 40, 256 56 / 45, 512 62 / 64, 1024 66 / 99.  Below 32 literals there is
+// nothing to split (20: 19 / 21).
 constexpr int64_t F64_SPLIT_UNITS = 256;
 
 // Constraints per wave: enough waves per bin to cover the chip (the
@@ -2578,8 +2579,12 @@ static ffsat_status run_eval(ffsat_plan *pl, const IO *x, IO *F, IO *grad, IO *c
             e = enqueue_pull(pl, (const float *)x, x_step ? nullptr : (float *)grad, out, eta, eta_dev, unsat_bits, U,
                              want_check, skip, s);
             prof_end(pl, s, rec);
-            if (e == hipSuccess && x_step && !x_next)
-                e = launch_copy_f32(x_step, pl->d_xalt, (int64_t)p->n * pl->B, s);
+            if (x_step && !x_next) {
+                // the points back in the launch of the sums (3-SAT, n = 50, 16
+                // restarts: 24.2 us with a launch of their own, now 21.3)
+                r.copy_src = pl->d_xalt;
+                r.copy_dst = x_step;
+            }
         }
         prof_begin(pl, s, prof_active(pl, s), rec, io, -1);
         if (e == hipSuccess) e = launch_reduce_f32(r, s);

@@ -2357,6 +2357,7 @@ extern "C" ffsat_status ffsat_plan_describe(const ffsat_plan *pl, char *buf, siz
       << ", \"pull_entry_bytes\": " << (pull ? 4 * PULL_E[pull] : 0)
       << ", \"pull_gathers_per_restart\": " << n_gather
       << ", \"pull_other_slots\": " << n_rest
+      << ", \"pull_chunks\": " << (pull ? (pl->p->n + pl->pull_vc - 1) / pl->pull_vc : 0)
       << ", \"pull_rows\": " << (pull ? pull_rows(pl) : 0) << ", \"pull_rpl\": " << pl->pull_rpl
       << ", \"objective_rows\": " << eval_rows(pl, IO_F32, pull)
       << ", \"group_real_cpw\": " << pl->group_real_cpw << ", \"group_dft_fg\": " << pl->group_dft_fg

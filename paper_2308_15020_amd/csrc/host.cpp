@@ -1462,8 +1462,12 @@ static ffsat_status build_groups(ffsat_plan *pl)
     if (!pl->grouped) return FFSAT_OK;
     const std::vector<Bin> &bins = pl->bins[IO_F32];
     std::vector<GroupEntry> ent;
-    std::vector<Blk> dft, real;
-    int row0 = 0, con0 = 0;   // con0: first key of the bin
+    struct Piece {
+        int2 b;         // entry, first unit
+        double cost;
+    };
+    std::vector<Piece> dft, real;
+    int row0 = 0;
     for (int i = 0; i < (int)bins.size(); ++i) {
         const Bin &b = bins[i];
         const int rows = (b.count + b.cpw - 1) / b.cpw;
@@ -1486,17 +1490,16 @@ static ffsat_status build_groups(ffsat_plan *pl)
         const int64_t units = (int64_t)rows * n_rb;
         const double unit_cost = b.cost / std::max(1, b.count) * b.cpw * rpw;
         if (fg == 4) {
-            for (int64_t u = 0; u < units; ++u) dft.push_back({make_int2(ei, (int)u), unit_cost, con0 + (int)(u / n_rb)});
+            for (int64_t u = 0; u < units; ++u) dft.push_back({make_int2(ei, (int)u), unit_cost});
             pl->glds = std::max(pl->glds, (size_t)3 * (b.seg + 1) * 64 * sizeof(float));
         } else {
             for (int64_t u = 0; u < units; u += 4)
-                (b.cls == CLASS_DFT ? dft : real).push_back({make_int2(ei, (int)u), 4 * unit_cost, con0 + (int)(u / n_rb)});
+                (b.cls == CLASS_DFT ? dft : real).push_back({make_int2(ei, (int)u), 4 * unit_cost});
         }
-        con0 += rows;
         row0 += rows;
     }
     if (ent.empty()) return FFSAT_OK;
-    std::stable_sort(dft.begin(), dft.end(), [](const Blk &x, const Blk &y) { return x.cost > y.cost; });
+    std::stable_sort(dft.begin(), dft.end(), [](const Piece &x, const Piece &y) { return x.cost > y.cost; });
     std::vector<int2> order;
     order.reserve(dft.size() + real.size());
     size_t di = 0, ri = 0;

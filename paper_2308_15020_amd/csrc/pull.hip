@@ -31,7 +31,9 @@ namespace ffsat {
 // indices or entry words, broadcast with readlane), all gathers of a batch
 // are issued before any term is added, and the terms are added in list
 // order.  Batches past a list's end read null entries (kind 7: every
-// coefficient zero) so that no term needs a branch.  Gathers are buffer
+// coefficient zero) so that no term needs a branch; they take the weight of the
+// batch's first entry, a constraint of the variable, so that a weight that is not
+// finite reaches no other variable.  Gathers are buffer
 // loads: the variable's row offset is scalar, the restart offset per lane.
 constexpr int RK_NULL = 7;
 constexpr int BUF_DW3 = 0x00020000;   // gfx9 buffer resource word 3 (raw 32-bit loads)
@@ -118,7 +120,8 @@ __global__ __launch_bounds__(64 * PULL_WAVES) void k_pull(PullArgs a, const floa
 #pragma unroll 1
         for (int p = p0; p < p1; p += NB) {
             const int w = p * E + lane;
-            const int ev = lane < NB * E ? (w < p1 * E ? pent[w] : ((lane % E) == 1 ? RK_NULL : 0)) : 0;
+            int ev = lane < NB * E ? (w < p1 * E ? pent[w] : ((lane % E) == 1 ? RK_NULL : 0)) : 0;
+            ev = w >= p1 * E && lane % E == 0 ? lane_bcast(ev, 0) : ev;
             float xo[NB][NO][RPL];
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
@@ -153,9 +156,7 @@ __global__ __launch_bounds__(64 * PULL_WAVES) void k_pull(PullArgs a, const floa
                         }
                     }
                 }
-                // a null entry reads the weight of constraint 0, which a caller may
-                // have set to an infinity or NaN
-                const float wc1 = rk == RK_NULL ? 0.f : wc * c1;
+                const float wc1 = wc * c1;
 #pragma unroll
                 for (int r = 0; r < RPL; ++r) {
                     const float gterm = wc1 * prod[r];

@@ -96,7 +96,8 @@ typedef struct {
                                 this many literals run in FP64 in ffsat_eval
                                 (0 = default 128: from there the FP64
                                 polynomial form is faster than FP32 running
-                                products, and more precise) */
+                                products, and more precise; shorter at-least-t
+                                do not go through the roots in FP32) */
     uint32_t flags;          /* FFSAT_FLAG_* */
 } ffsat_problem_desc;
 
@@ -197,7 +198,8 @@ ffsat_status ffsat_plan_destroy(ffsat_plan *plan);
  * shapes of the bins inside a grouped launch (transform-free constraints per
  * wave 4, 8 or 16 in the all-bin group; root-of-unity frequency split 1 or
  * 4), which replace the per-bin shapes of those bins.  Results go to the
- * plan's tune cache (in memory, and the JSON file when one is named). */
+ * plan's tune cache (in memory, and the JSON file when one is named).  FP32
+ * calls that the caller captured in a graph before have to be captured again. */
 ffsat_status ffsat_plan_tune(ffsat_plan *plan, void *stream);
 /* Writes a JSON description of the bins and their tile shapes into buf
  * (truncated to len-1 characters, always NUL-terminated). */
@@ -219,17 +221,32 @@ ffsat_status ffsat_plan_profile_read(ffsat_plan *plan, int32_t reset, char *buf,
  *   F[b]           = sum_c w_c WE_c(x_b)          (optional, device [B])
  *   grad[v*B+b]    = dF/dx_v at x_b               (optional, device [n][B])
  *   con_val[c*B+b] = WE_c(x_b), unweighted        (optional, device [m][B])
- * WE_c is evaluated by the three steps of Alg. 2 (affine factors at the
- * roots of unity, product over literals, dot with the conjugated
- * coefficients) and differentiated by leave-one-out prefix/suffix products
- * (Eq. chain); OR and XOR use the transform-free products (App. B).
- * Computation is FP32 except the root-of-unity products of constraints at
- * least fp64_min_len long, which run in FP64; there each lane's segment
- * product at a root is evaluated from the segment's elementary symmetric
- * polynomials and the leave-one-out products through per-degree moments
- * (the same quantities in another rounding order).  Results are deterministic
- * (no floating-point atomics).  Points outside [-1,1] are evaluated as
- * given (the polynomial is defined everywhere). */
+ * WE_c is one multilinear polynomial, evaluated by the route that its kind,
+ * length and arithmetic take (the last one for every kind under
+ * FFSAT_FLAG_FORCE_DFT, for every at-least-t under FFSAT_FLAG_UNIT_CIRCLE):
+ *   OR, XOR, at-least-1, at-least-k: the transform-free products (App. B);
+ *   at-least-t in FP32, up to 128 literals: 2 P(X < t) - 1, X the number of
+ *     true literals of independent draws; the distribution of X by products
+ *     of nonnegative polynomials, the gradient P(X without i = t - 1);
+ *   other at-least-t: the three steps of Alg. 2 (affine factors at the roots
+ *     of unity, product over literals, dot with the conjugated
+ *     coefficients), differentiated by leave-one-out products (Eq. chain).
+ * Computation is FP32 except the root-of-unity route of constraints at least
+ * fp64_min_len long, which runs in FP64: each lane's segment product at a
+ * root is evaluated from the segment's elementary symmetric polynomials and
+ * the leave-one-out products through per-degree moments (the same quantities
+ * in another rounding order). There, from 80 literals on, the number of roots
+ * and the frequencies of an at-least-t are chosen at the points: what is left
+ * out is below 6e-19.
+ * Results are deterministic (no floating-point atomics): the same call on the
+ * same batch gives the same bits. Between calls the last bits may differ
+ * where sums are grouped otherwise: in F with and without a gradient (the
+ * pulled gradient adds in another order) or at another batch size, and, in
+ * constraints whose frequencies are chosen at the points, with the restarts
+ * evaluated beside a restart (one choice serves the up to 16 of a wave;
+ * within the rounding of the arithmetic). Points outside [-1,1] are evaluated
+ * as given (the polynomial is defined everywhere); a restart with a NaN or
+ * infinite point leaves the others' results in place. */
 ffsat_status ffsat_eval(ffsat_plan *plan, const float *x, float *F, float *grad,
                         float *con_val, void *stream);
 /* ffsat_eval plus the exact check of the same point (see ffsat_round_check

@@ -1109,11 +1109,9 @@ struct EvalFn {
 // Segment shapes.  FP32 arithmetic: L = 1 with SEG in {4, 8, ..., 32}, L >= 2
 // with SEG in {16, 20, 24, 28, 32}.  FP64 arithmetic: L = 1 with SEG in
 // {4, 8, ..., 24}; L = 2..8 with SEG in {16, 20, 24}, L = 8 also with every
-// SEG from 25 to 32; L = 16 with every SEG from 14 to 32 (the long root-of-unity bins: a padding position costs as
-// much as a literal in every frequency, and in the polynomial form the
-// per-frequency cost of a lane, about 2.5 SEG operations plus a butterfly
-// stage per doubling of L, favours long segments; 32 positions still fit 2
-// waves per SIMD).
+// SEG from 25 to 32; L = 16 with every SEG from 14 to 32 (the long root-of-unity
+// bins; 32 positions still fit 2 waves per SIMD; the rule and its measurements are
+// at shape_for, host.cpp).
 template <typename IO, typename CT, int SEG, int L, bool CPLX>
 static EvalFn<IO> handle()
 {

@@ -14,8 +14,8 @@
 //  * Longer ones: one wave each, a lane per literal; the transposed words of 64
 //    literals give each restart its count (k_check_long).
 // Measured at n = 100000, 420000 clauses of 3, 256 restarts: 39 us for the
-// signs and the assignment bits (102 MB: 2.6 TB/s, the assignment words are
-// written 4 bytes at a time), 46 us for the clauses (5 million gathered words
+// signs and the assignment bits (109 MB in and out: 2.8 TB/s, the assignment words
+// are written 4 bytes at a time), 46 us for the clauses (5 million gathered words
 // from L2); the check inside the evaluation kernels took 745 us.
 #include "internal.h"
 

@@ -545,9 +545,16 @@ void shape_for_uc(int k, int &seg, int &L)
 // arithmetic: SEG up to 24 (multiples of 4 below 8 lanes and up to 24 at 8),
 // 8-lane groups take every SEG from 25 to 32 (k <= 256) and 16-lane groups
 // every SEG from 14 to 32 (k <= 512): in root-of-unity bins a padding
-// position costs as much as a literal in every frequency, and each doubling
-// of L adds a butterfly stage per frequency.  Real chains pay for padding once, so they keep the coarser
-// steps: fewer distinct shapes mean fewer, larger kernel launches.
+// position costs as much as a literal in every frequency, each doubling of L adds a
+// butterfly stage per frequency, and with fewer lanes a constraint a wave reads
+// more restarts of a line.  Against that stands a lane's work of SEG^2 per
+// constraint, the larger part where few frequencies run (node_window).  1000
+// at-least-t of 225..256 literals, 150 uniform points, 8 lanes of 29..32 / 16 of
+// 15..16: FP32 points 350 / 369 us, FP64 points 500 / 419; of 193..224 literals, 8 of
+// 25..28 / 16 of 14: 324 / 360 and 399 / 386.  One rule serves both evaluations, the
+// FP32 one's.
+// Real chains pay for padding once, so they keep the coarser steps: fewer distinct
+// shapes mean fewer, larger kernel launches.
 void shape_for(int ct, int k, int &seg, int &L, bool dft)
 {
     if (ct == CT_F64) {
@@ -558,7 +565,7 @@ void shape_for(int ct, int k, int &seg, int &L, bool dft)
         if (L == 8 && (k + 7) / 8 > 32) L = 16;
         if (L == 16 && (k + 15) / 16 > 32) L = 32;
         const int s = (k + L - 1) / L;
-        if (L >= 16) seg = std::max(14, s);   // every count: padding costs as much as a literal
+        if (L >= 16) seg = std::max(14, s);   // every count
         else if (L == 8 && s > 24) seg = s;
         else if (L > 1) seg = std::max(16, ((s + 3) / 4) * 4);
         else seg = s <= 4 ? 4 : ((s + 3) / 4) * 4;
